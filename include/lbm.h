@@ -206,7 +206,12 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
 /* Advance every plate by n_steps time steps (Fig. 4: accelerations,
  * Newmark update, boundary reset, LBE with the second-row rule, and the
  * synchronization after every l-th step).  Stream-ordered and asynchronous:
- * returns once the work is enqueued.  With two-step tilings part of the work
+ * returns once the work is enqueued.  Several steps are taken per launch in
+ * patches held in registers (block passes) unless a plate uses readings other
+ * than R1 + M1, a body is too dense in boundary nodes to be cut into patches,
+ * or lbm_set_tiling asked for one step per launch; the tile launches of a
+ * tiling (lbm_set_tiling) serve those cases, with the same results bit for
+ * bit.  With two-step tile launches part of the work
  * runs on a second stream of the library's that forks from and joins back
  * into the context's stream with events within the call (see
  * lbm_use_overlap), so to the caller the work is ordered on the context's
@@ -301,7 +306,10 @@ lbm_status lbm_info(const lbm_ctx *ctx, lbm_info_t *info);
  *             multiple of align nodes that fits (strip starts aligned to
  *             align nodes, so that every row segment a tile writes covers
  *             whole cache lines);
- *  steps      1 (or 0): one time step per launch; 2: tiles with no boundary
+ *  steps      1 (or 0): one time step per launch; 2: several steps per pass --
+ *             block passes where the bodies allow them (see lbm_step), which
+ *             do not depend on the other values, else tile launches in which
+ *             tiles with no boundary
  *             or second-row node within two nodes of their area take two
  *             time steps per pass over HBM (the other tiles take the two
  *             steps in two launches); a tile then owns at most lanes-4
@@ -344,7 +352,9 @@ lbm_status lbm_set_tiling(lbm_ctx *ctx, const lbm_tiling *tiling);
  * default) -- overlapped (frame tiles of their own edge rows, 2 and 4 rows);
  * the fastest one-stream tiling is kept unless an overlapped one is at least
  * 3 % faster (then overlap is turned on, else off).  Nontemporal stores are
- * not tried when the state fits in the 256 MB Infinity Cache.  The result
+ * not tried when the state fits in the 256 MB Infinity Cache.  Block passes
+ * (see lbm_step) are timed last and used if they are faster than the best
+ * tiling.  The result
  * applies to this context only (every context starts from the same default
  * tiling, whatever ran before in the process).  best_ms (nullable) receives
  * the fastest interior time per step (for two-step tilings half the time of
@@ -359,10 +369,13 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, double *best_ms);
  * step), ms[1] boundary/second-row, ms[2] synchronization, ms[3] two-step
  * interior launches (the first launch of a pair: two steps of the two-step
  * tiles -- of the frame tiles only when the pair is overlapped -- and one of
- * the others), ms[4] the deep-tile launches of overlapped pairs (see
+ * the others) or block passes, ms[4] the deep-tile launches of overlapped pairs (see
  * lbm_use_overlap); and the number of launches of each kind in
  * launches[0..4] (nullable).  Overlapped launches run at the same time, so
- * the sum over kinds can exceed the wall time.  Synchronizes the stream. */
+ * the sum over kinds can exceed the wall time.  After lbm_set_tiling or
+ * lbm_autotune the tile launches of that tiling are run and timed (also where
+ * lbm_step uses block passes), else what lbm_step launches.  Synchronizes the
+ * stream. */
 lbm_status lbm_profile(lbm_ctx *ctx, int64_t n_steps, double *ms, int64_t *launches);
 
 /* Capture, without running them, the HIP graphs that lbm_step(ctx,

@@ -7,10 +7,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
-SOURCES = [os.path.join(CSRC, "lbm_kernels.hip"), os.path.join(CSRC, "lbm_host.cpp"),
-           os.path.join(CSRC, "lbm_geom.cpp"), os.path.join(CSRC, "lbm_probe.hip")]
-HEADERS = [os.path.join(CSRC, "lbm_types.h"), os.path.join(CSRC, "lbm_kernels.h"),
-           os.path.join(ROOT, "include", "lbm.h")]
+SOURCES = [os.path.join(CSRC, f) for f in ("lbm_kernels.hip", "lbm_block.hip", "lbm_host.cpp",
+                                           "lbm_geom.cpp", "lbm_probe.hip")]
+HEADERS = [os.path.join(CSRC, f) for f in ("lbm_types.h", "lbm_kernels.h", "lbm_device.h",
+                                           "lbm_patches.h")]
+HEADERS.append(os.path.join(ROOT, "include", "lbm.h"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -1,0 +1,475 @@
+// lbm_block.hip -- several time steps of a patch per pass (gfx950).
+//
+// k_block advances every plate by up to K steps in one launch.  A workgroup
+// of eight waves owns a rectangle of nodes and holds it, with the halo its K
+// steps depend on, in registers: lane = column (64 of them), each wave M
+// consecutive rows, every node's populations and u, du/dt in its lane.  All
+// steps are taken there -- collide, pull, acceleration, update of u, the
+// boundary reset, the second-row rule and the boundary accelerations -- and
+// only the owned nodes of t + K are written.  What the halo's outer nodes
+// compute after their neighbourhood is missing never reaches an owned node
+// (the host derives the halo from the method's dependences).
+//
+// Neighbours: along x through wave shifts (no LDS), along y in the lane's own
+// registers, across waves through one LDS row per wave and side.  In a patch
+// with boundary nodes u is kept in LDS; every thread takes at most one node
+// whose gradient the boundary needs (a boundary node's thread goes on to its
+// reset field and to the population its second-row neighbours pull, eq.
+// LBE_mod; one value per field, since J = 0 at boundary nodes under reading R1
+// and the four moving populations are equal), and the eighth wave takes the
+// boundary accelerations from the gradient nodes' stresses, one lane per node,
+// beside the seven others' march.  (With the whole boundary work in that one
+// wave, five gradients per node, a step of a patch with boundary nodes took
+// 11 us instead of 2.)
+//
+// Why: one launch per step costs 14 us on the smallest plates whatever their
+// size (launch gap, then a serial chain of dependent memory reads), and a
+// large plate moves its whole state every step; here a step costs one to
+// three barriers and no memory traffic.  Measured in FP64, us per step, one
+// launch per step -> four steps per pass: 64^2 periodic 14.1 -> 4.1, 97^2
+// with loads 14.0 -> 6.9, 1024^2 clamped 51 -> 23, 4096^2 with a hole 805 ->
+// 295 (F16DEV 474 -> 234).  Small plates are bound by the pass's latency
+// (launch, one load, the steps' chains), large ones by the halo (1.5x the
+// reads) and by loading and computing in turn: one workgroup fills a CU's
+// registers.
+#include <hip/hip_runtime.h>
+
+#include "../../include/lbm.h"
+#include "lbm_device.h"
+#include "lbm_kernels.h"
+#include "lbm_types.h"
+
+namespace lbm {
+namespace {
+
+constexpr int kWaves = kBlockThreads / 64;
+
+// The value of lane - 1 (shift_e) / lane + 1 (shift_w); 0 past the end.
+__device__ __forceinline__ float from_west(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float from_east(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double from_west(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double from_east(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, false));
+}
+
+// Per field of a boundary node: the reset field and the population pulled
+// from it.
+template <class C>
+struct BndOut {
+  C fld[2], pull[2];
+};
+// State of a boundary node between steps: u, du/dt, and its boundary data.
+template <class U>
+struct BndState {
+  U u[4];
+  double val[2];  // (FP64 whatever U: the amplitude multiplies it in FP64)
+  U cell[5];
+  int32_t kind, load;
+};
+
+template <class U>
+struct alignas(2 * sizeof(U)) Vec2 {
+  U x, y;
+};
+
+template <class CD, int M>
+struct BlockLds {
+  using C = typename CD::C;
+  using U = typename CD::U;
+  // [step parity][wave][0: its first row, 1: its last row][rho phi, rho psi,
+  // population leaving across that row phi, psi][lane]
+  C edge[2][kWaves][2][4][64];
+  // patches with boundary nodes (seven interior waves)
+  Vec2<U> u[64 * M * (kWaves - 1)];      // displacement of the patch
+  uint16_t task[64 * M * (kWaves - 1)];  // boundary task of a node + 1, 0 elsewhere
+  PTask rec[kBlockTasks];
+  BndState<U> st[kBlockTasks];
+  U stress[kBlockGrads][3];
+  BndOut<C> out[kBlockTasks];
+};
+
+// Finite-difference gradient (d_x u_x, d_y u_x, d_x u_y, d_y u_y) at patch
+// node l (stencil codes as in GradNode) from the displacements in LDS.
+// (Nodes whose stencil leaves the patch are never needed; their indices are
+// clamped.)
+template <class U>
+__device__ __forceinline__ void patch_grad(const Vec2<U> *us, int l, int code, int last,
+                                           const PlateDev &P, U g[4]) {
+  const int cx = code & 7, cy = (code >> 3) & 7;
+  auto far = [&](int c, int d, int &a, int &b) {
+    const bool fwd = c == FD_CENTRAL || c == FD_FWD3 || c == FD_FWD2, bwd = c == FD_BWD3 || c == FD_BWD2;
+    a = l + (fwd ? d : bwd ? -d : 0);
+    b = l + (c == FD_CENTRAL ? -d : c == FD_FWD3 ? 2 * d : c == FD_BWD3 ? -2 * d : 0);
+    a = a < 0 ? 0 : a > last ? last : a;
+    b = b < 0 ? 0 : b > last ? last : b;
+  };
+  int xa, xb, ya, yb;
+  far(cx, 1, xa, xb);
+  far(cy, 64, ya, yb);
+  const Vec2<U> q0 = us[l], qxa = us[xa], qxb = us[xb], qya = us[ya], qyb = us[yb];
+  g[0] = fd_vals<U>(cx, q0.x, qxa.x, qxb.x, P);
+  g[1] = fd_vals<U>(cy, q0.x, qya.x, qyb.x, P);
+  g[2] = fd_vals<U>(cx, q0.y, qxa.y, qxb.y, P);
+  g[3] = fd_vals<U>(cy, q0.y, qya.y, qyb.y, P);
+}
+
+// The gradient node of a thread (patches with boundary nodes) and, if that is
+// a boundary node, its rest and moving population of the previous step.
+template <class CD>
+struct GradDuty {
+  using C = typename CD::C;
+  using U = typename CD::U;
+  int l = -1, code = 0, task = -1;
+  C fo[2][2];
+
+  __device__ __forceinline__ void load(const DevState &s, const BlockArgs &a, const Patch &t,
+                                       const PlateDev &P) {
+    if ((int)threadIdx.x >= t.g1 - t.g0) return;
+    const PGrad G = a.grads[t.g0 + (int)threadIdx.x];
+    l = G.l;
+    code = G.code;
+    task = G.task;
+    if (task < 0) return;
+    const int64_t k = s.bnd[a.tasks[t.b0 + task].bnd].node;
+#pragma unroll
+    for (int fl = 0; fl < 2; fl++) {
+      typename CD::Slot r5[5];
+      C f[5];
+      CD::load_raw(s, a.in, fl, k, r5);
+      CD::raw_to_pops(P, fl, r5, f);
+      fo[fl][0] = f[0];
+      fo[fl][1] = f[1];
+    }
+  }
+
+  // Stress at the node from u in LDS and, if reset, a boundary node's reset
+  // fields and f~ -- the average of its populations of this step and the
+  // previous one -- collided towards its own equilibrium (eq. LBE_mod; J = 0).
+  template <class L>
+  __device__ __forceinline__ void run(const PlateDev &P, L &lds, int last, bool reset) {
+    if (l < 0) return;
+    U g[4], sg[3];
+    patch_grad<U>(lds.u, l, code, last, P, g);
+    hooke<U>(P, g, sg[0], sg[1], sg[2]);
+#pragma unroll
+    for (int q = 0; q < 3; q++) lds.stress[threadIdx.x][q] = sg[q];
+    if (!reset || task < 0) return;
+    BndOut<C> o;
+#pragma unroll
+    for (int fl = 0; fl < 2; fl++) {
+      o.fld[fl] = fl == 0 ? (C)(g[0] + g[3]) : (C)(g[2] - g[1]);
+      C fn[5], f[5], r, fc[5];
+      CD::eq_pops(P, fl, o.fld[fl], C(0), C(0), fn);
+      f[0] = C(0.5) * (fn[0] + fo[fl][0]);
+#pragma unroll
+      for (int q = 1; q < 5; q++) f[q] = C(0.5) * (fn[q] + fo[fl][1]);
+      collide_pops<CD>(P, fl, f, r, fc);
+      o.pull[fl] = fc[1];
+      fo[fl][0] = fn[0];
+      fo[fl][1] = fn[1];
+    }
+    lds.out[task] = o;
+  }
+};
+
+// The boundary accelerations of a patch, by its last wave; the barriers are
+// those of block_march<BND>.
+template <class CD, int M>
+__device__ __forceinline__ void block_boundary(const DevState &s, const BlockArgs &a, const Patch &t,
+                                               const PlateDev &P, BlockLds<CD, M> &lds) {
+  using U = typename CD::U;
+  constexpr int kLast = 64 * M * (kWaves - 1) - 1;
+  const int lane = threadIdx.x & 63;
+  const int nb = t.b1 - t.b0;
+  const unsigned long long n0 = s.counter[a.in];
+  GradDuty<CD> duty;
+  duty.load(s, a, t, P);
+  for (int i = lane; i < nb; i += 64) {
+    const PTask T = a.tasks[t.b0 + i];
+    const BndNode B = s.bnd[T.bnd];
+    BndState<U> S;
+    S.u[0] = ldg<U>(s.u[a.in][0], B.node);
+    S.u[1] = ldg<U>(s.u[a.in][1], B.node);
+    S.u[2] = ldg<U>(s.v[a.in][0], B.node);
+    S.u[3] = ldg<U>(s.v[a.in][1], B.node);
+    S.val[0] = B.val[0];
+    S.val[1] = B.val[1];
+#pragma unroll
+    for (int q = 0; q < 5; q++) S.cell[q] = (U)B.cell[q];
+    S.kind = B.kind;
+    S.load = B.load;
+    lds.rec[i] = T;
+    lds.st[i] = S;
+  }
+  __syncthreads();  // (u in LDS, task map cleared)
+  for (int i = lane; i < nb; i += 64) lds.task[lds.rec[i].l] = (uint16_t)(i + 1);
+  duty.run(P, lds, kLast, false);
+  __syncthreads();
+  for (int j = 0; j < a.steps; j++) {
+    const unsigned long long n = n0 + (unsigned long long)j;
+    const Kick<U> kick = kick_of<U>(P, n == 0);
+    // accelerations at t_n; u, du/dt of t_{n+1} (nothing reads u in LDS here)
+    for (int i = lane; i < nb; i += 64) {
+      const PTask T = lds.rec[i];
+      BndState<U> &S = lds.st[i];
+      const U ux = S.u[0], uy = S.u[1], vx = S.u[2], vy = S.u[3];
+      U ax, ay;
+      if (S.kind == LBM_BC_DIRICHLET) {
+        const double g = load_amp(s, S.load, (double)(n + 1) * P.dt);
+        dirichlet_accel<U>(P, n, (U)(g * S.val[0]), (U)(g * S.val[1]), ux, uy, vx, vy, ax, ay);
+      } else {
+        const double g = load_amp(s, S.load, (double)n * P.dt);
+        U sk[3], sr[4][3];
+        bool has[4];
+#pragma unroll
+        for (int q = 0; q < 3; q++) sk[q] = lds.stress[T.g[0]][q];
+#pragma unroll
+        for (int d = 0; d < 4; d++) {
+          has[d] = T.g[1 + d] >= 0;
+          const int gi = has[d] ? T.g[1 + d] : T.g[0];
+#pragma unroll
+          for (int q = 0; q < 3; q++) sr[d][q] = lds.stress[gi][q];
+        }
+        const U l4[4] = {S.cell[1], S.cell[2], S.cell[3], S.cell[4]};
+        neumann_accel<U>(P, sk, has, sr, S.cell[0], l4, (U)(g * S.val[0]), (U)(g * S.val[1]), ax,
+                         ay);
+      }
+      U q[4];
+      newmark<U>(P, kick, ax, ay, ux, uy, vx, vy, q[0], q[1], q[2], q[3]);
+#pragma unroll
+      for (int c = 0; c < 4; c++) S.u[c] = q[c];
+      lds.u[T.l] = Vec2<U>{q[0], q[1]};
+      if (T.own && (!(fabs((double)q[0]) < 1e30) || !(fabs((double)q[1]) < 1e30))) s.flag[0] = 1;
+    }
+    __syncthreads();
+    __syncthreads();
+    duty.run(P, lds, kLast, true);
+    __syncthreads();
+  }
+  for (int i = lane; i < nb; i += 64)
+    if (lds.rec[i].own) {
+      const int64_t k = s.bnd[lds.rec[i].bnd].node;
+      stg<U>(s.u[a.out][0], k, lds.st[i].u[0]);
+      stg<U>(s.u[a.out][1], k, lds.st[i].u[1]);
+      stg<U>(s.v[a.out][0], k, lds.st[i].u[2]);
+      stg<U>(s.v[a.out][1], k, lds.st[i].u[3]);
+    }
+}
+
+// The interior waves of a patch; BND: it holds boundary nodes (the last wave
+// is block_boundary's).
+template <class CD, int M, bool BND>
+__device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &a, const Patch &t,
+                                            const PlateDev &P, BlockLds<CD, M> &lds) {
+  using C = typename CD::C;
+  using U = typename CD::U;
+  using Slot = typename CD::Slot;
+  constexpr int kW = BND ? kWaves - 1 : kWaves;
+  constexpr int kLast = 64 * M * kW - 1;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const unsigned long long n0 = s.counter[a.in];
+
+  // ---- the state of t: row r = wv M + m of the patch, column lane (lanes and
+  // rows past the patch repeat its last one)
+  auto wrap = [](int i, int n) { return i < 0 || i >= n ? ((i % n) + n) % n : i; };
+  const int x = wrap(t.ex + (lane < t.ew ? lane : t.ew - 1), P.nx);
+  auto node = [&](int m) {
+    const int r = wv * M + m;
+    return node_of(P, x, wrap(t.ey + (r < t.eh ? r : t.eh - 1), P.ny));
+  };
+  GradDuty<CD> duty;
+  if constexpr (BND) duty.load(s, a, t, P);
+  uint8_t cl[M];
+  Slot raw[M][2][5];
+  U uv[M][4];
+#pragma unroll
+  for (int m = 0; m < M; m++) {
+    const int64_t k = node(m);
+    cl[m] = BND ? s.cls[k] : (uint8_t)CL_IN;
+    CD::load_raw(s, a.in, 0, k, raw[m][0]);
+    CD::load_raw(s, a.in, 1, k, raw[m][1]);
+    uv[m][0] = ldg<U>(s.u[a.in][0], k);
+    uv[m][1] = ldg<U>(s.u[a.in][1], k);
+    uv[m][2] = ldg<U>(s.v[a.in][0], k);
+    uv[m][3] = ldg<U>(s.v[a.in][1], k);
+  }
+  if constexpr (BND) {
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+      const int l = (wv * M + m) * 64 + lane;
+      if (lane >= t.ew || wv * M + m >= t.eh) cl[m] = 0;
+      lds.u[l] = Vec2<U>{uv[m][0], uv[m][1]};
+      lds.task[l] = 0;
+      if (!(cl[m] & CL_IN)) {
+#pragma unroll
+        for (int fl = 0; fl < 2; fl++)
+#pragma unroll
+          for (int q = 0; q < 5; q++) raw[m][fl][q] = Slot(0);
+      }
+    }
+    __syncthreads();
+    duty.run(P, lds, kLast, false);
+    __syncthreads();
+  }
+
+  for (int j = 0; j < a.steps; j++) {
+    const Kick<U> kick = kick_of<U>(P, n0 + (unsigned long long)j == 0);
+    const int par = j & 1;
+    // ---- collide; hand the first and last row to the neighbouring waves
+    C rho[M][2], fs[M][2][5];
+#pragma unroll
+    for (int m = 0; m < M; m++)
+#pragma unroll
+      for (int fl = 0; fl < 2; fl++) CD::collide_raw(P, fl, raw[m][fl], rho[m][fl], fs[m][fl]);
+#pragma unroll
+    for (int fl = 0; fl < 2; fl++) {
+      lds.edge[par][wv][0][fl][lane] = rho[0][fl];
+      lds.edge[par][wv][0][2 + fl][lane] = fs[0][fl][4];
+      lds.edge[par][wv][1][fl][lane] = rho[M - 1][fl];
+      lds.edge[par][wv][1][2 + fl][lane] = fs[M - 1][fl][2];
+    }
+    __syncthreads();
+    // ---- interior acceleration, u and du/dt of t_{n+1}
+    C lo[4], hi[4];  // the rows below and above this wave's
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      lo[q] = wv > 0 ? lds.edge[par][wv > 0 ? wv - 1 : 0][1][q][lane] : C(0);
+      hi[q] = wv < kW - 1 ? lds.edge[par][wv < kW - 1 ? wv + 1 : wv][0][q][lane] : C(0);
+    }
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+      const C e0 = from_east(rho[m][0]), w0 = from_west(rho[m][0]);
+      const C e1 = from_east(rho[m][1]), w1 = from_west(rho[m][1]);
+      const C nn0 = m + 1 < M ? rho[m + 1 < M ? m + 1 : m][0] : hi[0];
+      const C nn1 = m + 1 < M ? rho[m + 1 < M ? m + 1 : m][1] : hi[1];
+      const C ss0 = m > 0 ? rho[m > 0 ? m - 1 : 0][0] : lo[0];
+      const C ss1 = m > 0 ? rho[m > 0 ? m - 1 : 0][1] : lo[1];
+      U q[4];
+      interior_update<U>(P, kick, (U)e0, (U)w0, (U)nn0, (U)ss0, (U)e1, (U)w1, (U)nn1, (U)ss1, uv[m][0],
+                         uv[m][1], uv[m][2], uv[m][3], q[0], q[1], q[2], q[3]);
+#pragma unroll
+      for (int c = 0; c < 4; c++) uv[m][c] = q[c];
+      if constexpr (BND) {
+        if ((cl[m] & (CL_IN | CL_B)) == CL_IN)
+          lds.u[(wv * M + m) * 64 + lane] = Vec2<U>{q[0], q[1]};
+      }
+    }
+    if constexpr (BND) {
+      __syncthreads();
+      duty.run(P, lds, kLast, true);
+      __syncthreads();
+    }
+    // ---- pull: f_alpha(x, t + dt) = f*_alpha(x - c^alpha dt)
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+      C f[2][5];
+#pragma unroll
+      for (int fl = 0; fl < 2; fl++) {
+        f[fl][0] = fs[m][fl][0];
+        f[fl][1] = from_west(fs[m][fl][1]);
+        f[fl][3] = from_east(fs[m][fl][3]);
+        f[fl][2] = m > 0 ? fs[m > 0 ? m - 1 : 0][fl][2] : lo[2 + fl];
+        f[fl][4] = m + 1 < M ? fs[m + 1 < M ? m + 1 : m][fl][4] : hi[2 + fl];
+      }
+      if constexpr (BND) {
+        const int l = (wv * M + m) * 64 + lane;
+        if (cl[m] & CL_S) {
+#pragma unroll
+          for (int al = 1; al < 5; al++) {
+            const int off = al == 1 ? -1 : al == 2 ? -64 : al == 3 ? 1 : 64;
+            const int lu = l + off;
+            const int ti = lu < 0 || lu > kLast ? 0 : (int)lds.task[lu];
+            if (ti) {
+              f[0][al] = lds.out[ti - 1].pull[0];
+              f[1][al] = lds.out[ti - 1].pull[1];
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int fl = 0; fl < 2; fl++) CD::encode(P, fl, f[fl], raw[m][fl]);
+      if constexpr (BND) {
+        if (cl[m] & CL_B) {
+          const int ti = (int)lds.task[(wv * M + m) * 64 + lane];
+          if (ti) {
+#pragma unroll
+            for (int fl = 0; fl < 2; fl++) CD::eq_raw(P, fl, lds.out[ti - 1].fld[fl], raw[m][fl]);
+          }
+        }
+      }
+    }
+  }
+
+  // ---- the owned nodes of t + K (u, du/dt of boundary nodes: block_boundary)
+#pragma unroll
+  for (int m = 0; m < M; m++) {
+    const int r = wv * M + m;
+    if (lane >= t.ox0 && lane < t.ox1 && r >= t.oy0 && r < t.oy1 && (cl[m] & CL_IN)) {
+      const int64_t k = node(m);
+      CD::store_raw(s, a.out, 0, k, raw[m][0]);
+      CD::store_raw(s, a.out, 1, k, raw[m][1]);
+      if (!BND || !(cl[m] & CL_B)) {
+        stg<U>(s.u[a.out][0], k, uv[m][0]);
+        stg<U>(s.u[a.out][1], k, uv[m][1]);
+        stg<U>(s.v[a.out][0], k, uv[m][2]);
+        stg<U>(s.v[a.out][1], k, uv[m][3]);
+      }
+    }
+  }
+}
+
+template <int ST, int M>
+__global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArgs a) {
+  using CD = typename CodecOf<ST>::type;
+  __shared__ BlockLds<CD, M> lds;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    s.counter[a.out] = s.counter[a.in] + (unsigned long long)a.steps;
+  const int ix = tile_index(blockIdx.x, a.q);
+  if (ix >= a.n) return;
+  const Patch t = a.patches[ix];
+  const PlateDev P = s.plates[t.plate];
+  if (t.b1 <= t.b0)
+    block_march<CD, M, false>(s, a, t, P, lds);
+  else if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < kWaves - 1)  // (a scalar branch)
+    block_march<CD, M, true>(s, a, t, P, lds);
+  else
+    block_boundary<CD, M>(s, a, t, P, lds);
+}
+
+template <int ST>
+hipError_t launch_block_t(const DevState &s, const BlockArgs &a, int rows, hipStream_t st) {
+  const dim3 grid(8 * a.q), th(kBlockThreads);
+  switch (rows) {
+    case 2: hipLaunchKernelGGL((k_block<ST, 2>), grid, th, 0, st, s, a); break;
+    case 4: hipLaunchKernelGGL((k_block<ST, 4>), grid, th, 0, st, s, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_block(int storage, const DevState &s, const Patch *patches, int n, int rows,
+                        const PTask *tasks, const PGrad *grads, int in, int out, int steps,
+                        hipStream_t st) {
+  if (n < 1 || steps < 1) return hipErrorInvalidValue;
+  const BlockArgs a{patches, tasks, grads, n, (n + 7) / 8, in, out, steps};
+  switch (storage) {
+    case LBM_STORE_F64: return launch_block_t<LBM_STORE_F64>(s, a, rows, st);
+    case LBM_STORE_F32: return launch_block_t<LBM_STORE_F32>(s, a, rows, st);
+    case LBM_STORE_F32DEV: return launch_block_t<LBM_STORE_F32DEV>(s, a, rows, st);
+    case LBM_STORE_F16DEV: return launch_block_t<LBM_STORE_F16DEV>(s, a, rows, st);
+    case LBM_STORE_BF16DEV: return launch_block_t<LBM_STORE_BF16DEV>(s, a, rows, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace lbm

@@ -21,6 +21,7 @@
 
 #include "../../include/lbm.h"
 #include "lbm_kernels.h"
+#include "lbm_patches.h"
 #include "lbm_types.h"
 
 using namespace lbm;
@@ -169,6 +170,21 @@ struct lbm_ctx {
   int prev = 1;  // buffer holding the boundary populations of t_{step-1}
   bool started = false;
   bool bnd_dirty = true;
+
+  // Block passes (k_block): several steps of every plate per launch, in place
+  // of the tile launches.  can_block: the plan was made (see plan_blocks);
+  // block: in use -- from the start, and under a tiling with steps = 2, which
+  // asks for several steps per pass; not under one with steps = 1.
+  PatchPlan plan;
+  bool can_block = false;
+  bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
+  Patch *d_patches = nullptr;
+  PTask *d_ptasks = nullptr;
+  PGrad *d_pgrads = nullptr;
+  bool block = false;
+  // the boundary nodes' u(t_{step+1}) is in the buffers the next step writes
+  // (the tile launches expect it there; the block pass computes it itself)
+  bool ahead = false;
 
   bool use_graphs = true;
   // Captured step graphs, keyed by what the launch sequence of k steps from
@@ -1237,6 +1253,25 @@ hipError_t enqueue_segment(lbm_ctx *c, int64_t s, int64_t k, int &cur, int &prev
   };
   const int T = 2;  // intermediate buffer of a two-step pair
   hipError_t e = hipSuccess;
+  if (c->block) {
+    for (int64_t n = s; n < s + k && e == hipSuccess;) {
+      const int q = (int)std::min<int64_t>(c->plan.K, s + k - n), in = cur;
+      e = timed(3, st, [&] {
+        return launch_block(c->storage, c->ds, c->d_patches, (int)c->plan.patches.size(),
+                            c->plan.rows, c->d_ptasks, c->d_pgrads, in, in ^ 1, q, st);
+      });
+      prev = cur;
+      cur ^= 1;
+      n += q;
+    }
+    if (e == hipSuccess && c->sync_every > 0 && (s + k) % c->sync_every == 0) {
+      const int b = cur;
+      e = timed(2, st, [&] {
+        return launch_sync(c->storage, c->ds, c->d_tiles, (int)c->ltiles.size(), c->lanes, b, st);
+      });
+    }
+    return e;
+  }
   bool pend_d = false;  // a deep launch that st has not waited for: ev_d[par ^ 1]
   bool have_f = false;  // ev_f[par ^ 1] marks what the next deep launch waits for
   int par = 0;          // parity of the pair (events alternate)
@@ -1343,7 +1378,10 @@ void advance_buffers(const lbm_ctx *c, int64_t s, int64_t n, int &cur, int &prev
   while (n > 0) {
     const int64_t k = segment_limit(c, s, n);
     for (int64_t m = s; m < s + k;) {
-      if (c->two && s + k - m >= 2) {
+      if (c->block) {
+        prev = cur;
+        m += std::min<int64_t>(c->plan.K, s + k - m);
+      } else if (c->two && s + k - m >= 2) {
         prev = 2;
         m += 2;
       } else {
@@ -1534,14 +1572,71 @@ lbm_status start(lbm_ctx *c) {
                            hipMemcpyHostToDevice),
               "plate upload");
   }
-  // boundary accelerations of step 0: u(t_1) of the boundary nodes, into
-  // both buffers the first step may write
-  HIP_TRY(c, launch_boundary(c->storage, c->ds, c->d_chunks, (int)c->chunks.size(), c->d_unodes,
-                             c->d_gnodes, c->d_btasks, c->d_stasks, c->cur, c->prev, c->cur ^ 1,
-                             have_third(c) ? 2 : -1, 0, 0, c->stream),
-          "first boundary step");
   c->started = true;
   return LBM_OK;
+}
+
+// Boundary accelerations of the next step at a complete state that has none:
+// the boundary nodes' u(t_{step+1}), into the buffers a tile launch may write.
+lbm_status ensure_ahead(lbm_ctx *c) {
+  if (c->ahead) return LBM_OK;
+  HIP_TRY(c, launch_boundary(c->storage, c->ds, c->d_chunks, (int)c->chunks.size(), c->d_unodes,
+                             c->d_gnodes, c->d_btasks, c->d_stasks, c->cur, c->prev, c->cur ^ 1,
+                             have_third(c) ? 2 : -1, (int)(c->step & 1), 0, c->stream),
+          "boundary accelerations");
+  c->ahead = true;
+  return LBM_OK;
+}
+
+// What has to be in place before steps are enqueued from the current state;
+// a block pass leaves no boundary accelerations for the next step.
+lbm_status before_steps(lbm_ctx *c) {
+  if (!c->block) return ensure_ahead(c);
+  c->ahead = false;
+  return LBM_OK;
+}
+
+// Steps per block pass and rows per wave of its patches.
+constexpr int kBlockSteps = 4, kBlockRows = 4;
+
+// Cut the plates for the block pass and upload the plan (lbm_create).  False
+// if the tile launches have to do (the context stays usable): a plate whose
+// boundary nodes lie so densely that the nodes a small rectangle depends on do
+// not fit a patch, or no memory for the plan.
+bool plan_blocks(lbm_ctx *c, int K, int rows) {
+  std::vector<PatchPlate> v(c->ph.size());
+  for (size_t p = 0; p < v.size(); p++) {
+    const PlateHost &h = c->ph[p];
+    v[p].index = (int)p;
+    v[p].nx = h.nx;
+    v[p].ny = h.ny;
+    v[p].px = h.px;
+    v[p].py = h.py;
+    v[p].cls = h.cls.data();
+    v[p].bnd = c->bnd.data() + h.b0;
+    v[p].b0 = h.b0;
+    v[p].nb = h.b1 - h.b0;
+  }
+  if (!make_patch_plan(v, K, rows, c->plan) || c->plan.patches.empty()) return false;
+  const PatchPlan &pl = c->plan;
+  c->d_patches = (Patch *)dev_alloc(c, pl.patches.size() * sizeof(Patch));
+  c->d_ptasks = (PTask *)dev_alloc(c, std::max<size_t>(1, pl.tasks.size()) * sizeof(PTask));
+  c->d_pgrads = (PGrad *)dev_alloc(c, std::max<size_t>(1, pl.grads.size()) * sizeof(PGrad));
+  auto up = [](void *d, const void *h, size_t bytes) {
+    return d && (bytes == 0 || hipMemcpy(d, h, bytes, hipMemcpyHostToDevice) == hipSuccess);
+  };
+  if (!up(c->d_patches, pl.patches.data(), pl.patches.size() * sizeof(Patch)) ||
+      !up(c->d_ptasks, pl.tasks.data(), pl.tasks.size() * sizeof(PTask)) ||
+      !up(c->d_pgrads, pl.grads.data(), pl.grads.size() * sizeof(PGrad))) {
+    dev_free(c, c->d_patches);
+    dev_free(c, c->d_ptasks);
+    dev_free(c, c->d_pgrads);
+    c->d_patches = nullptr;
+    c->d_ptasks = nullptr;
+    c->d_pgrads = nullptr;
+    return false;
+  }
+  return true;
 }
 
 // Rough magnitude of the initial fields for the 16-bit scale.
@@ -1897,6 +1992,7 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   build_tile_tables(c);
   if (upload_tiles(c) != LBM_OK || upload_tile_tables(c) != LBM_OK)
     return bail(LBM_E_NOMEM, c->err);
+  if (!c->variant_readings) c->block = c->can_block = plan_blocks(c, kBlockSteps, kBlockRows);
   if (hipHostMalloc((void **)&c->h_flag, sizeof(int), hipHostMallocDefault) != hipSuccess)
     return bail(LBM_E_NOMEM, "pinned flag allocation failed");
   *c->h_flag = 0;
@@ -1974,6 +2070,10 @@ lbm_status lbm_step(lbm_ctx *c, int64_t n) {
   if (st) return st;
   st = start(c);
   if (st) return st;
+  if (n > 0) {
+    st = before_steps(c);
+    if (st) return st;
+  }
   while (n > 0) {
     if (c->use_graphs) {
       const int64_t k = graph_chunk(c, c->step, n);
@@ -2172,7 +2272,9 @@ lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
   c->align = align;
   c->nt = stream;
   c->two = steps == 2 ? 1 : 0;
-  if (c->two) {
+  c->tiled = true;
+  c->block = c->can_block && c->two;
+  if (c->two && !c->block) {
     lbm_status st3 = ensure_third(c);
     if (st3) {
       c->two = 0;
@@ -2216,6 +2318,19 @@ lbm_status lbm_profile(lbm_ctx *c, int64_t n, double *ms, int64_t *launches) {
   lbm_status st = check_flag(c, false);
   if (st) return st;
   st = start(c);
+  if (st) return st;
+  // (with a tiling of the caller's, its tile launches are what is timed)
+  struct Restore {
+    lbm_ctx *c;
+    bool block;
+    ~Restore() { c->block = block; }
+  } restore{c, c->block};
+  if (c->tiled) c->block = false;
+  if (!c->block && c->two) {
+    st = ensure_third(c);
+    if (st) return st;
+  }
+  st = before_steps(c);
   if (st) return st;
   // Launches on one stream go back to back; the time between the events
   // around a launch is its device time plus the gap to the previous
@@ -2273,7 +2388,11 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   // buffer neither launch writes and a state of t_n that does not come from
   // a synchronization (nor n = 0): otherwise one real step is taken first.
   const bool syncs_now = c->sync_every > 0 && c->step % c->sync_every == 0;
-  if (c->step == 0 || (syncs_now && c->sync_every > 1) || c->prev == 2) {
+  const bool fresh = !c->ahead;  // (a block pass leaves no populations of t_{n-1} either)
+  c->block = false;
+  st = ensure_ahead(c);
+  if (st) return st;
+  if (fresh || c->step == 0 || (syncs_now && c->sync_every > 1) || c->prev == 2) {
     HIP_TRY(c, enqueue_segment(c, c->step, 1, c->cur, c->prev, c->stream, nullptr),
             "step launch");
     c->syncs_done += syncs_in(c, c->step, 1);
@@ -2585,6 +2704,23 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
       }
     }
   }
+  // The block pass, timed as lbm_step runs it (from buffer cur to the other
+  // one, which the steps below write anyway).
+  bool use_block = false;
+  if (c->can_block) {
+    reps = std::max(steps, std::min(400, (int)std::ceil(5.0 / std::max(best, 1e-4) / c->plan.K)));
+    const double per = time_body([&](hipStream_t st2, int k) {
+      hipError_t e = hipSuccess;
+      for (int i = 0; i < k && e == hipSuccess; i++)
+        e = launch_block(c->storage, c->ds, c->d_patches, (int)c->plan.patches.size(), c->plan.rows,
+                         c->d_ptasks, c->d_pgrads, cur, cur ^ 1, c->plan.K, st2);
+      return e;
+    }, true) / c->plan.K;
+    if (per < best) {
+      best = per;
+      use_block = true;
+    }
+  }
   // The second launch of a pair wrote the boundary nodes' u(t_{n+2}) where
   // the next step expects u(t_{n+1}): recompute that from u(t_n).
   HIP_TRY(c, launch_boundary(c->storage, c->ds, c->d_chunks, (int)c->chunks.size(), c->d_unodes,
@@ -2605,7 +2741,9 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   c->nt = bt.stream_stores;
   c->two = bt.steps == 2 ? 1 : 0;
   c->overlap = best_ov;
-  if (!c->two && !had_third) release_third(c);
+  c->block = use_block;
+  c->tiled = true;
+  if ((!c->two || c->block) && !had_third) release_third(c);
   build_tiles(c);
   build_tile_tables(c);
   st = upload_tiles(c);

@@ -18,6 +18,14 @@ hipError_t launch_interior(int storage, const DevState &s, const Tile *tiles, in
 // and is never the run's first step.
 hipError_t launch_deep(int storage, const DevState &s, const Tile *tiles, int ntiles, int lanes,
                        const StepBufs &b, hipStream_t stream);
+// The block pass: `steps` steps of every plate from the complete state in
+// buffer `in` to the complete state in `out` (n patches of at most 8 * rows
+// rows, whose halos are for at least `steps` steps; rows: 2 or 4).  (Weak, so
+// that host-only programs link the runtime without the kernels.)
+hipError_t launch_block(int storage, const DevState &s, const Patch *patches, int n, int rows,
+                        const PTask *tasks, const PGrad *grads, int in, int out, int steps,
+                        hipStream_t stream)
+    __attribute__((weak));
 // Boundary kernel over nchunks chunks (see k_boundary): the boundary work of
 // step n - 1 on the state of t_n in buffer bc (resets and second-row pulls
 // only if do_reset).

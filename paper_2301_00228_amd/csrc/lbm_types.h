@@ -230,4 +230,51 @@ struct Prologue {
   int enabled;
 };
 
+// One workgroup of the block pass (k_block): the patch of ew x eh nodes from
+// (ex, ey) (not wrapped: may be negative or past the plate on a periodic
+// axis) whose nodes [ox0, ox1) x [oy0, oy1) (patch coordinates) it owns, its
+// boundary tasks [b0, b1) (none: a patch of interior nodes) and the gradient
+// nodes [g0, g1) they read.
+struct Patch {
+  int32_t plate, ex, ey, ew, eh;
+  int32_t ox0, ox1, oy0, oy1;
+  int32_t b0, b1, g0, g1;
+  int32_t pad;
+};
+
+// A boundary node of a patch: its record, its place in the patch (row * 64 +
+// column), whether the patch owns it, and the gradient nodes (relative to the
+// patch's) of the node and of its E, N, W, S neighbours (-1: not in the body).
+struct PTask {
+  int32_t bnd;
+  uint16_t l;
+  uint16_t own;
+  int16_t g[5];
+  int16_t pad;
+};
+
+// A body node of a patch whose displacement gradient the boundary tasks
+// need: its place, its task (-1: an interior node), its stencil code (as
+// GradNode.code).
+struct PGrad {
+  uint16_t l;
+  int16_t task;
+  uint16_t code;
+  uint16_t pad;
+};
+
+struct BlockArgs {
+  const Patch *patches;
+  const PTask *tasks;
+  const PGrad *grads;
+  int n, q;       // patches, patches per XCD
+  int in, out;    // state buffers of t and t + steps
+  int steps;
+};
+
+constexpr int kBlockThreads = 512;  // threads of a block-pass workgroup
+constexpr int kBlockCols = 64;      // columns of a patch at most
+constexpr int kBlockTasks = 256;    // boundary nodes of a patch at most
+constexpr int kBlockGrads = kBlockThreads;  // gradient nodes of a patch at most
+
 }  // namespace lbm
