@@ -26,12 +26,19 @@
 // size (launch gap, then a serial chain of dependent memory reads), and a
 // large plate moves its whole state every step; here a step costs one to
 // three barriers and no memory traffic.  Measured in FP64, us per step, one
-// launch per step -> four steps per pass: 64^2 periodic 14.1 -> 4.1, 97^2
-// with loads 14.0 -> 6.9, 1024^2 clamped 51 -> 23, 4096^2 with a hole 805 ->
-// 295 (F16DEV 474 -> 234).  Small plates are bound by the pass's latency
+// launch per step -> four steps per pass: 64^2 periodic 14.1 -> 3.6, 97^2
+// with loads 14.0 -> 6.1, 1024^2 clamped 51 -> 20, 4096^2 with a hole 805 ->
+// 289 (F16DEV 474 -> 222).  Small plates are bound by the pass's latency
 // (launch, one load, the steps' chains), large ones by the halo (1.5x the
 // reads) and by loading and computing in turn: one workgroup fills a CU's
 // registers.
+//
+// A step's chain is kept short by what does not change from step to step: a
+// gradient node's stencil (its two neighbours and coefficients per axis) and a
+// second-row node's upwind boundary nodes are looked up once per pass, and the
+// pull asks per row and direction, wave-uniformly, whether any lane has one.
+// (Looked up in every step they took 1.5k to 4.3k cycles of about 8k; 97^2
+// with loads 6.9 us per step, 1024^2 in F32 16.)
 #include <hip/hip_runtime.h>
 
 #include "../../include/lbm.h"
@@ -44,20 +51,16 @@ namespace {
 
 constexpr int kWaves = kBlockThreads / 64;
 
-// The value of lane - 1 (shift_e) / lane + 1 (shift_w); 0 past the end.
-__device__ __forceinline__ float from_west(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float from_east(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));
-}
+// The value of lane - 1 (from_west) / lane + 1 (from_east); 0 past the end.
+__device__ __forceinline__ int lane_shift_w(int v) { return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int lane_shift_e(int v) { return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ float from_west(float v) { return __int_as_float(lane_shift_w(__float_as_int(v))); }
+__device__ __forceinline__ float from_east(float v) { return __int_as_float(lane_shift_e(__float_as_int(v))); }
 __device__ __forceinline__ double from_west(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false));
+  return __hiloint2double(lane_shift_w(__double2hiint(v)), lane_shift_w(__double2loint(v)));
 }
 __device__ __forceinline__ double from_east(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, false));
+  return __hiloint2double(lane_shift_e(__double2hiint(v)), lane_shift_e(__double2loint(v)));
 }
 
 // Per field of a boundary node: the reset field and the population pulled
@@ -96,30 +99,35 @@ struct BlockLds {
   BndOut<C> out[kBlockTasks];
 };
 
-// Finite-difference gradient (d_x u_x, d_y u_x, d_x u_y, d_y u_y) at patch
-// node l (stencil codes as in GradNode) from the displacements in LDS.
-// (Nodes whose stencil leaves the patch are never needed; their indices are
-// clamped.)
-template <class U>
-__device__ __forceinline__ void patch_grad(const Vec2<U> *us, int l, int code, int last,
-                                           const PlateDev &P, U g[4]) {
-  const int cx = code & 7, cy = (code >> 3) & 7;
-  auto far = [&](int c, int d, int &a, int &b) {
-    const bool fwd = c == FD_CENTRAL || c == FD_FWD3 || c == FD_FWD2, bwd = c == FD_BWD3 || c == FD_BWD2;
-    a = l + (fwd ? d : bwd ? -d : 0);
-    b = l + (c == FD_CENTRAL ? -d : c == FD_FWD3 ? 2 * d : c == FD_BWD3 ? -2 * d : 0);
+// One axis of a finite-difference stencil at patch node l, from its code:
+// ((c[0] q + c[1] qa) + c[2] qb) times 1/(2 dh) or 1/dh, with q at l, qa, qb at
+// a, b (the coefficients of fd_vals; small integers, so kept in FP32).  Nodes
+// whose stencil leaves the patch are never needed; their indices are clamped.
+struct AxisStencil {
+  int a, b;
+  float c[3];
+  bool half;  // 1/(2 dh)
+  __device__ __forceinline__ void set(int code, int l, int d, int last) {
+    const bool cen = code == FD_CENTRAL, f3 = code == FD_FWD3, b3 = code == FD_BWD3;
+    const bool f2 = code == FD_FWD2, b2 = code == FD_BWD2;
+    a = l + ((cen || f3 || f2) ? d : (b3 || b2) ? -d : 0);
+    b = l + (cen ? -d : f3 ? 2 * d : b3 ? -2 * d : 0);
     a = a < 0 ? 0 : a > last ? last : a;
     b = b < 0 ? 0 : b > last ? last : b;
-  };
-  int xa, xb, ya, yb;
-  far(cx, 1, xa, xb);
-  far(cy, 64, ya, yb);
-  const Vec2<U> q0 = us[l], qxa = us[xa], qxb = us[xb], qya = us[ya], qyb = us[yb];
-  g[0] = fd_vals<U>(cx, q0.x, qxa.x, qxb.x, P);
-  g[1] = fd_vals<U>(cy, q0.x, qya.x, qyb.x, P);
-  g[2] = fd_vals<U>(cx, q0.y, qxa.y, qxb.y, P);
-  g[3] = fd_vals<U>(cy, q0.y, qya.y, qyb.y, P);
-}
+    c[0] = f3 ? -3.0f : b3 ? 3.0f : f2 ? -1.0f : b2 ? 1.0f : 0.0f;
+    c[1] = (cen || f2) ? 1.0f : f3 ? 4.0f : b3 ? -4.0f : b2 ? -1.0f : 0.0f;
+    c[2] = (cen || f3) ? -1.0f : b3 ? 1.0f : 0.0f;
+    half = cen || f3 || b3;
+  }
+  template <class U>
+  __device__ __forceinline__ void apply(const Vec2<U> *us, const Vec2<U> &q, const PlateDev &P, U &dx,
+                                        U &dy) const {
+    const Vec2<U> qa = us[a], qb = us[b];
+    const U c0 = (U)c[0], ca = (U)c[1], cb = (U)c[2], sc = half ? (U)P.inv_2h : (U)P.inv_h;
+    dx = ((c0 * q.x + ca * qa.x) + cb * qb.x) * sc;
+    dy = ((c0 * q.y + ca * qa.y) + cb * qb.y) * sc;
+  }
+};
 
 // The gradient node of a thread (patches with boundary nodes) and, if that is
 // a boundary node, its rest and moving population of the previous step.
@@ -127,15 +135,17 @@ template <class CD>
 struct GradDuty {
   using C = typename CD::C;
   using U = typename CD::U;
-  int l = -1, code = 0, task = -1;
+  int l = -1, task = -1;
+  AxisStencil sx, sy;
   C fo[2][2];
 
   __device__ __forceinline__ void load(const DevState &s, const BlockArgs &a, const Patch &t,
-                                       const PlateDev &P) {
+                                       const PlateDev &P, int last) {
     if ((int)threadIdx.x >= t.g1 - t.g0) return;
     const PGrad G = a.grads[t.g0 + (int)threadIdx.x];
     l = G.l;
-    code = G.code;
+    sx.set(G.code & 7, l, 1, last);
+    sy.set((G.code >> 3) & 7, l, kBlockCols, last);
     task = G.task;
     if (task < 0) return;
     const int64_t k = s.bnd[a.tasks[t.b0 + task].bnd].node;
@@ -154,10 +164,12 @@ struct GradDuty {
   // fields and f~ -- the average of its populations of this step and the
   // previous one -- collided towards its own equilibrium (eq. LBE_mod; J = 0).
   template <class L>
-  __device__ __forceinline__ void run(const PlateDev &P, L &lds, int last, bool reset) {
+  __device__ __forceinline__ void run(const PlateDev &P, L &lds, bool reset) {
     if (l < 0) return;
-    U g[4], sg[3];
-    patch_grad<U>(lds.u, l, code, last, P, g);
+    U g[4], sg[3];  // d_x u_x, d_y u_x, d_x u_y, d_y u_y
+    const Vec2<U> q0 = lds.u[l];
+    sx.apply(lds.u, q0, P, g[0], g[2]);
+    sy.apply(lds.u, q0, P, g[1], g[3]);
     hooke<U>(P, g, sg[0], sg[1], sg[2]);
 #pragma unroll
     for (int q = 0; q < 3; q++) lds.stress[threadIdx.x][q] = sg[q];
@@ -191,7 +203,7 @@ __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArg
   const int nb = t.b1 - t.b0;
   const unsigned long long n0 = s.counter[a.in];
   GradDuty<CD> duty;
-  duty.load(s, a, t, P);
+  duty.load(s, a, t, P, kLast);
   for (int i = lane; i < nb; i += 64) {
     const PTask T = a.tasks[t.b0 + i];
     const BndNode B = s.bnd[T.bnd];
@@ -211,7 +223,7 @@ __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArg
   }
   __syncthreads();  // (u in LDS, task map cleared)
   for (int i = lane; i < nb; i += 64) lds.task[lds.rec[i].l] = (uint16_t)(i + 1);
-  duty.run(P, lds, kLast, false);
+  duty.run(P, lds, false);
   __syncthreads();
   for (int j = 0; j < a.steps; j++) {
     const unsigned long long n = n0 + (unsigned long long)j;
@@ -251,7 +263,7 @@ __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArg
     }
     __syncthreads();
     __syncthreads();
-    duty.run(P, lds, kLast, true);
+    duty.run(P, lds, true);
     __syncthreads();
   }
   for (int i = lane; i < nb; i += 64)
@@ -286,7 +298,13 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
     return node_of(P, x, wrap(t.ey + (r < t.eh ? r : t.eh - 1), P.ny));
   };
   GradDuty<CD> duty;
-  if constexpr (BND) duty.load(s, a, t, P);
+  if constexpr (BND) duty.load(s, a, t, P, kLast);
+  // task + 1 (0: none) of a boundary node (low half of up[0]) or of a second-row
+  // node's upwind boundary nodes W, S, E, N; which (row, direction) any lane of
+  // the wave has, and which rows hold boundary nodes
+  uint32_t up[M][2], some = 0, some_b = 0;
+#pragma unroll
+  for (int m = 0; m < M; m++) up[m][0] = up[m][1] = 0;
   uint8_t cl[M];
   Slot raw[M][2][5];
   U uv[M][4];
@@ -316,8 +334,24 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
       }
     }
     __syncthreads();
-    duty.run(P, lds, kLast, false);
+    duty.run(P, lds, false);
     __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+      const int l = (wv * M + m) * 64 + lane;
+      // (a node past the patch has no task, and no needed node has one there)
+      auto task_at = [&](int k) { return k < 0 || k > kLast ? 0u : (uint32_t)lds.task[k]; };
+      if (cl[m] & CL_B) up[m][0] = task_at(l);
+      if (cl[m] & CL_S) {
+        up[m][0] = task_at(l - 1) | task_at(l - 64) << 16;
+        up[m][1] = task_at(l + 1) | task_at(l + 64) << 16;
+      }
+      some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][0] & 0xffffu)) ? 1 : 0) << (4 * m);
+      some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][0] >> 16)) ? 2 : 0) << (4 * m);
+      some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][1] & 0xffffu)) ? 4 : 0) << (4 * m);
+      some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][1] >> 16)) ? 8 : 0) << (4 * m);
+      some_b |= (uint32_t)(__any((cl[m] & CL_B) != 0) ? 1 : 0) << m;
+    }
   }
 
   for (int j = 0; j < a.steps; j++) {
@@ -364,7 +398,7 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
     }
     if constexpr (BND) {
       __syncthreads();
-      duty.run(P, lds, kLast, true);
+      duty.run(P, lds, true);
       __syncthreads();
     }
     // ---- pull: f_alpha(x, t + dt) = f*_alpha(x - c^alpha dt)
@@ -380,28 +414,30 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
         f[fl][4] = m + 1 < M ? fs[m + 1 < M ? m + 1 : m][fl][4] : hi[2 + fl];
       }
       if constexpr (BND) {
-        const int l = (wv * M + m) * 64 + lane;
-        if (cl[m] & CL_S) {
+        // populations pulled from boundary nodes (eq. LBE_mod)
 #pragma unroll
-          for (int al = 1; al < 5; al++) {
-            const int off = al == 1 ? -1 : al == 2 ? -64 : al == 3 ? 1 : 64;
-            const int lu = l + off;
-            const int ti = lu < 0 || lu > kLast ? 0 : (int)lds.task[lu];
-            if (ti) {
-              f[0][al] = lds.out[ti - 1].pull[0];
-              f[1][al] = lds.out[ti - 1].pull[1];
-            }
+        for (int al = 1; al < 5; al++)
+          if (some >> (4 * m + al - 1) & 1u) {
+            const uint32_t w2 = up[m][(al - 1) >> 1];
+            const uint32_t ti = cl[m] & CL_S ? ((al - 1) & 1 ? w2 >> 16 : w2 & 0xffffu) : 0u;
+            const BndOut<C> &o = lds.out[ti ? ti - 1 : 0];
+            const C p0 = o.pull[0], p1 = o.pull[1];
+            f[0][al] = ti ? p0 : f[0][al];
+            f[1][al] = ti ? p1 : f[1][al];
           }
-        }
       }
 #pragma unroll
       for (int fl = 0; fl < 2; fl++) CD::encode(P, fl, f[fl], raw[m][fl]);
       if constexpr (BND) {
-        if (cl[m] & CL_B) {
-          const int ti = (int)lds.task[(wv * M + m) * 64 + lane];
-          if (ti) {
+        if (some_b >> m & 1u) {
+          const bool isb = (cl[m] & CL_B) && up[m][0];
+          const BndOut<C> &o = lds.out[isb ? up[m][0] - 1 : 0];
 #pragma unroll
-            for (int fl = 0; fl < 2; fl++) CD::eq_raw(P, fl, lds.out[ti - 1].fld[fl], raw[m][fl]);
+          for (int fl = 0; fl < 2; fl++) {
+            Slot q5[5];
+            CD::eq_raw(P, fl, o.fld[fl], q5);
+#pragma unroll
+            for (int q = 0; q < 5; q++) raw[m][fl][q] = isb ? q5[q] : raw[m][fl][q];
           }
         }
       }
@@ -432,13 +468,14 @@ __global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArg
   __shared__ BlockLds<CD, M> lds;
   if (blockIdx.x == 0 && threadIdx.x == 0)
     s.counter[a.out] = s.counter[a.in] + (unsigned long long)a.steps;
+  const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // (scalar branches)
   const int ix = tile_index(blockIdx.x, a.q);
   if (ix >= a.n) return;
   const Patch t = a.patches[ix];
   const PlateDev P = s.plates[t.plate];
   if (t.b1 <= t.b0)
     block_march<CD, M, false>(s, a, t, P, lds);
-  else if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < kWaves - 1)  // (a scalar branch)
+  else if (wv < kWaves - 1)
     block_march<CD, M, true>(s, a, t, P, lds);
   else
     block_boundary<CD, M>(s, a, t, P, lds);

@@ -75,14 +75,19 @@ __device__ __forceinline__ void stg(void *p, int64_t k, T v) {
     static_cast<T *>(p)[k] = v;
 }
 
+// One rounding for x y + z.  Used only where the product is exact (x a power
+// of two), so that the result is that of the separate operations.
+__device__ __forceinline__ double fma1(double x, double y, double z) { return __builtin_fma(x, y, z); }
+__device__ __forceinline__ float fma1(float x, float y, float z) { return __builtin_fmaf(x, y, z); }
+
 template <class C>
 __device__ __forceinline__ void eq_populations(C a0, C a, C rho, C jx, C jy, C f[5]) {
   const C ar = a * rho;
   f[0] = a0 * rho;
-  f[1] = ar + C(0.5) * jx;
-  f[2] = ar + C(0.5) * jy;
-  f[3] = ar - C(0.5) * jx;
-  f[4] = ar - C(0.5) * jy;
+  f[1] = fma1(C(0.5), jx, ar);
+  f[2] = fma1(C(0.5), jy, ar);
+  f[3] = fma1(C(-0.5), jx, ar);
+  f[4] = fma1(C(-0.5), jy, ar);
 }
 
 // Post-collision populations f* = f - 2 (f - f_eq(f)) and zeroth moment of
@@ -94,7 +99,7 @@ __device__ __forceinline__ void collide_populations(C a0, C a, const C f[5], C &
   C e[5];
   eq_populations<C>(a0, a, r, jx, jy, e);
 #pragma unroll
-  for (int q = 0; q < 5; q++) fs[q] = f[q] - C(2.0) * (f[q] - e[q]);
+  for (int q = 0; q < 5; q++) fs[q] = fma1(C(-2.0), f[q] - e[q], f[q]);
   rho = r;
 }
 
@@ -263,13 +268,14 @@ struct DevCodec {
   }
   __device__ static void moments_to_pops(const PlateDev &P, int fl, const float m[5], C f[5]) {
     const float q = m[4] + 4.0f * aw(P, fl) * m[0];
-    const float s13 = 0.5f * (q + m[3]);
-    const float s24 = 0.5f * (q - m[3]);
+    // f1 = ((q + N) / 2 + J_x) / 2 and so on (the halves are exact)
+    const float t13 = q + m[3], t24 = q - m[3];
+    const float hx = 0.5f * m[1], hy = 0.5f * m[2];
     f[0] = m[0] - q;
-    f[1] = 0.5f * (s13 + m[1]);
-    f[3] = 0.5f * (s13 - m[1]);
-    f[2] = 0.5f * (s24 + m[2]);
-    f[4] = 0.5f * (s24 - m[2]);
+    f[1] = fma1(0.25f, t13, hx);
+    f[3] = fma1(0.25f, t13, -hx);
+    f[2] = fma1(0.25f, t24, hy);
+    f[4] = fma1(0.25f, t24, -hy);
   }
   __device__ static void load(const DevState &s, int b, int fl, int64_t k, const PlateDev &P,
                               C f[5]) {
