@@ -1,37 +1,51 @@
 // lbm_block.hip -- several time steps of a patch per pass (gfx950).
 //
-// k_block advances every plate by up to K steps in one launch.  A workgroup
-// of eight waves owns a rectangle of nodes and holds it, with the halo its K
-// steps depend on, in registers: lane = column (64 of them), each wave M
-// consecutive rows, every node's populations and u, du/dt in its lane.  All
-// steps are taken there -- collide, pull, acceleration, update of u, the
-// boundary reset, the second-row rule and the boundary accelerations -- and
-// only the owned nodes of t + K are written.  What the halo's outer nodes
-// compute after their neighbourhood is missing never reaches an owned node
-// (the host derives the halo from the method's dependences).
+// A block pass advances every plate by up to K steps.  A workgroup owns a
+// rectangle of nodes and holds it, with the halo its K steps depend on, in
+// registers: lane = column (64 of them), each wave M consecutive rows, every
+// node's populations and u, du/dt in its lane.  All steps are taken there --
+// collide, pull, acceleration, update of u, the boundary reset, the second-row
+// rule and the boundary accelerations -- and only the owned nodes of t + K are
+// written.  What the halo's outer nodes compute after their neighbourhood is
+// missing never reaches an owned node (the host derives the halo from the
+// method's dependences).
 //
 // Neighbours: along x through wave shifts (no LDS), along y in the lane's own
-// registers, across waves through one LDS row per wave and side.  In a patch
-// with boundary nodes u is kept in LDS; every thread takes at most one node
-// whose gradient the boundary needs (a boundary node's thread goes on to its
-// reset field and to the population its second-row neighbours pull, eq.
-// LBE_mod; one value per field, since J = 0 at boundary nodes under reading R1
-// and the four moving populations are equal), and the eighth wave takes the
-// boundary accelerations from the gradient nodes' stresses, one lane per node,
-// beside the seven others' march.  (With the whole boundary work in that one
-// wave, five gradients per node, a step of a patch with boundary nodes took
-// 11 us instead of 2.)
+// registers, across row groups through one LDS row per group and side.
+//
+// k_block takes the patches with boundary nodes, and all patches of small
+// plates: eight waves, one workgroup per CU.  In a patch with boundary nodes u
+// is kept in LDS; every thread takes at most one node whose gradient the
+// boundary needs (a boundary node's thread goes on to its reset field and to the
+// population its second-row neighbours pull, eq. LBE_mod; one value per field,
+// since J = 0 at boundary nodes under reading R1 and the four moving populations
+// are equal), and the eighth wave takes the boundary accelerations from the
+// gradient nodes' stresses, one lane per node, beside the seven others' march.
+// (With the whole boundary work in that one wave, five gradients per node, a
+// step of a patch with boundary nodes took 11 us instead of 2.)  A step depends
+// on two nodes along a boundary and one across it, so a patch along an x edge is
+// tall: 32 columns, two row groups side by side in each wave, twice the rows (as
+// wide ones such patches owned 4 to 11 rows each of 28 to 42; 1024^2 was cut
+// into 418 patches with boundary nodes, now 146, 256 plates 3564 per 16, now 1212).
+//
+// k_inner takes the other patches of large plates with four waves and up to 256
+// registers per lane, so that two workgroups share a CU and one's loads and
+// stores run beside the other's steps (one workgroup of eight waves loaded and
+// computed in turn).  On small plates without boundary nodes it takes short
+// patches (eight waves of two rows): a step there takes as long as the rows of
+// a CU, 0.4 us each in FP64.
 //
 // Why: one launch per step costs 14 us on the smallest plates whatever their
 // size (launch gap, then a serial chain of dependent memory reads), and a
 // large plate moves its whole state every step; here a step costs one to
-// three barriers and no memory traffic.  Measured in FP64, us per step, one
-// launch per step -> four steps per pass: 64^2 periodic 14.1 -> 3.6, 97^2
-// with loads 14.0 -> 6.1, 1024^2 clamped 51 -> 20, 4096^2 with a hole 805 ->
-// 289 (F16DEV 474 -> 222).  Small plates are bound by the pass's latency
-// (launch, one load, the steps' chains), large ones by the halo (1.5x the
-// reads) and by loading and computing in turn: one workgroup fills a CU's
-// registers.
+// three barriers and no memory traffic.  Measured, us per step, one launch per
+// step -> k_block alone with K = 4 -> now: 64^2 periodic FP64 14.1 -> 3.6 -> 1.9,
+// 97^2 with loads 14.0 -> 6.1 -> 4.7, 1024^2 clamped 51 -> 20 -> 17, 4096^2 with
+// a hole 805 -> 289 -> 205, FP32 450 -> 163 -> 104, F16DEV 474 -> 222 -> 127.
+// Small plates are bound by the pass's latency (launch, one load, the steps'
+// chains); k_inner by memory in FP64 and F32DEV (4.8 TB/s of HBM, 1.6x to 1.8x the
+// state's reads), in FP32 by both that and the vector units (86 operations per
+// node and step, 85 % busy), in the 16-bit storages by their rounding (137).
 //
 // A step's chain is kept short by what does not change from step to step: a
 // gradient node's stencil (its two neighbours and coefficients per axis) and a
@@ -83,13 +97,17 @@ struct alignas(2 * sizeof(U)) Vec2 {
   U x, y;
 };
 
+// [step parity][0: a row group's first row, 1: its last row][rho phi, rho psi,
+// population leaving across that row phi, psi][group * w + column]
+template <class CD, int W>
+struct EdgeLds {
+  typename CD::C edge[2][2][4][64 * W];
+};
+
 template <class CD, int M>
-struct BlockLds {
+struct BlockLds : EdgeLds<CD, kWaves> {
   using C = typename CD::C;
   using U = typename CD::U;
-  // [step parity][wave][0: its first row, 1: its last row][rho phi, rho psi,
-  // population leaving across that row phi, psi][lane]
-  C edge[2][kWaves][2][4][64];
   // patches with boundary nodes (seven interior waves)
   Vec2<U> u[64 * M * (kWaves - 1)];      // displacement of the patch
   uint16_t task[64 * M * (kWaves - 1)];  // boundary task of a node + 1, 0 elsewhere
@@ -145,7 +163,7 @@ struct GradDuty {
     const PGrad G = a.grads[t.g0 + (int)threadIdx.x];
     l = G.l;
     sx.set(G.code & 7, l, 1, last);
-    sy.set((G.code >> 3) & 7, l, kBlockCols, last);
+    sy.set((G.code >> 3) & 7, l, t.w, last);
     task = G.task;
     if (task < 0) return;
     const int64_t k = s.bnd[a.tasks[t.b0 + task].bnd].node;
@@ -278,13 +296,12 @@ __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArg
 
 // The interior waves of a patch; BND: it holds boundary nodes (the last wave
 // is block_boundary's).
-template <class CD, int M, bool BND>
+template <class CD, int M, int kW, bool BND, class Lds>
 __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &a, const Patch &t,
-                                            const PlateDev &P, BlockLds<CD, M> &lds) {
+                                            const PlateDev &P, Lds &lds) {
   using C = typename CD::C;
   using U = typename CD::U;
   using Slot = typename CD::Slot;
-  constexpr int kW = BND ? kWaves - 1 : kWaves;
   constexpr int kLast = 64 * M * kW - 1;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const unsigned long long n0 = s.counter[a.in];
@@ -292,10 +309,26 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
   // ---- the state of t: row r = wv M + m of the patch, column lane (lanes and
   // rows past the patch repeat its last one)
   auto wrap = [](int i, int n) { return i < 0 || i >= n ? ((i % n) + n) % n : i; };
-  const int x = wrap(t.ex + (lane < t.ew ? lane : t.ew - 1), P.nx);
-  auto node = [&](int m) {
-    const int r = wv * M + m;
-    return node_of(P, x, wrap(t.ey + (r < t.eh ? r : t.eh - 1), P.ny));
+  // (the row groups of M rows: one per wave, two in a patch of w = 32 columns)
+  const int w = BND ? t.w : 64;
+  const int col = lane & (w - 1), grp = BND ? (int)(threadIdx.x / (unsigned)w) : wv;
+  const int at0 = grp * M * w + col;  // place of the lane's first node in the patch
+  // (what a pass of fewer steps does not depend on repeats nodes that it does)
+  const int h = BND ? kBlockCols : a.steps;
+  const int x0 = t.ox0 > h ? t.ox0 - h : 0, x1 = t.ox1 + h < t.ew ? t.ox1 + h : t.ew;
+  const int y0 = t.oy0 > h ? t.oy0 - h : 0, y1 = t.oy1 + h < t.eh ? t.oy1 + h : t.eh;
+  auto within = [](int i, int lo, int hi) { return i < lo ? lo : i < hi ? i : hi - 1; };
+  const int x = wrap(t.ex + within(col, x0, x1), P.nx);
+  auto node = [&](int m) { return node_of(P, x, wrap(t.ey + within(grp * M + m, y0, y1), P.ny)); };
+  // (away from boundary nodes only a node's own update reads its u and du/dt:
+  // the halo's lanes repeat an owned node's)
+  const int xo = wrap(t.ex + within(col, t.ox0, t.ox1), P.nx);
+  auto own_node = [&](int m) {
+    return node_of(P, xo, wrap(t.ey + within(grp * M + m, t.oy0, t.oy1), P.ny));
+  };
+  auto mine = [&](int m) {
+    const int r = grp * M + m;
+    return col >= t.ox0 && col < t.ox1 && r >= t.oy0 && r < t.oy1;
   };
   GradDuty<CD> duty;
   if constexpr (BND) duty.load(s, a, t, P, kLast);
@@ -314,16 +347,17 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
     cl[m] = BND ? s.cls[k] : (uint8_t)CL_IN;
     CD::load_raw(s, a.in, 0, k, raw[m][0]);
     CD::load_raw(s, a.in, 1, k, raw[m][1]);
-    uv[m][0] = ldg<U>(s.u[a.in][0], k);
-    uv[m][1] = ldg<U>(s.u[a.in][1], k);
-    uv[m][2] = ldg<U>(s.v[a.in][0], k);
-    uv[m][3] = ldg<U>(s.v[a.in][1], k);
+    const int64_t ku = BND ? k : own_node(m);
+    uv[m][0] = ldg<U>(s.u[a.in][0], ku);
+    uv[m][1] = ldg<U>(s.u[a.in][1], ku);
+    uv[m][2] = ldg<U>(s.v[a.in][0], ku);
+    uv[m][3] = ldg<U>(s.v[a.in][1], ku);
   }
   if constexpr (BND) {
 #pragma unroll
     for (int m = 0; m < M; m++) {
-      const int l = (wv * M + m) * 64 + lane;
-      if (lane >= t.ew || wv * M + m >= t.eh) cl[m] = 0;
+      const int l = at0 + m * w;
+      if (col >= t.ew || grp * M + m >= t.eh) cl[m] = 0;
       lds.u[l] = Vec2<U>{uv[m][0], uv[m][1]};
       lds.task[l] = 0;
       if (!(cl[m] & CL_IN)) {
@@ -338,13 +372,13 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < M; m++) {
-      const int l = (wv * M + m) * 64 + lane;
+      const int l = at0 + m * w;
       // (a node past the patch has no task, and no needed node has one there)
       auto task_at = [&](int k) { return k < 0 || k > kLast ? 0u : (uint32_t)lds.task[k]; };
       if (cl[m] & CL_B) up[m][0] = task_at(l);
       if (cl[m] & CL_S) {
-        up[m][0] = task_at(l - 1) | task_at(l - 64) << 16;
-        up[m][1] = task_at(l + 1) | task_at(l + 64) << 16;
+        up[m][0] = task_at(l - 1) | task_at(l - w) << 16;
+        up[m][1] = task_at(l + 1) | task_at(l + w) << 16;
       }
       some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][0] & 0xffffu)) ? 1 : 0) << (4 * m);
       some |= (uint32_t)(__any((cl[m] & CL_S) && (up[m][0] >> 16)) ? 2 : 0) << (4 * m);
@@ -357,44 +391,47 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
   for (int j = 0; j < a.steps; j++) {
     const Kick<U> kick = kick_of<U>(P, n0 + (unsigned long long)j == 0);
     const int par = j & 1;
-    // ---- collide; hand the first and last row to the neighbouring waves
+    // ---- collide; interior acceleration, u and du/dt of t_{n+1} of the rows
+    // between two of the lane's own (before the exchange: their neighbours' moments
+    // then need no registers after it); the first and last row go to the
+    // neighbouring groups
     C rho[M][2], fs[M][2][5];
-#pragma unroll
-    for (int m = 0; m < M; m++)
-#pragma unroll
-      for (int fl = 0; fl < 2; fl++) CD::collide_raw(P, fl, raw[m][fl], rho[m][fl], fs[m][fl]);
-#pragma unroll
-    for (int fl = 0; fl < 2; fl++) {
-      lds.edge[par][wv][0][fl][lane] = rho[0][fl];
-      lds.edge[par][wv][0][2 + fl][lane] = fs[0][fl][4];
-      lds.edge[par][wv][1][fl][lane] = rho[M - 1][fl];
-      lds.edge[par][wv][1][2 + fl][lane] = fs[M - 1][fl][2];
-    }
-    __syncthreads();
-    // ---- interior acceleration, u and du/dt of t_{n+1}
-    C lo[4], hi[4];  // the rows below and above this wave's
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      lo[q] = wv > 0 ? lds.edge[par][wv > 0 ? wv - 1 : 0][1][q][lane] : C(0);
-      hi[q] = wv < kW - 1 ? lds.edge[par][wv < kW - 1 ? wv + 1 : wv][0][q][lane] : C(0);
-    }
-#pragma unroll
-    for (int m = 0; m < M; m++) {
+    auto update = [&](int m, const C *ss, const C *nn) {
       const C e0 = from_east(rho[m][0]), w0 = from_west(rho[m][0]);
       const C e1 = from_east(rho[m][1]), w1 = from_west(rho[m][1]);
-      const C nn0 = m + 1 < M ? rho[m + 1 < M ? m + 1 : m][0] : hi[0];
-      const C nn1 = m + 1 < M ? rho[m + 1 < M ? m + 1 : m][1] : hi[1];
-      const C ss0 = m > 0 ? rho[m > 0 ? m - 1 : 0][0] : lo[0];
-      const C ss1 = m > 0 ? rho[m > 0 ? m - 1 : 0][1] : lo[1];
       U q[4];
-      interior_update<U>(P, kick, (U)e0, (U)w0, (U)nn0, (U)ss0, (U)e1, (U)w1, (U)nn1, (U)ss1, uv[m][0],
-                         uv[m][1], uv[m][2], uv[m][3], q[0], q[1], q[2], q[3]);
+      interior_update<U>(P, kick, (U)e0, (U)w0, (U)nn[0], (U)ss[0], (U)e1, (U)w1, (U)nn[1], (U)ss[1],
+                         uv[m][0], uv[m][1], uv[m][2], uv[m][3], q[0], q[1], q[2], q[3]);
 #pragma unroll
       for (int c = 0; c < 4; c++) uv[m][c] = q[c];
       if constexpr (BND) {
-        if ((cl[m] & (CL_IN | CL_B)) == CL_IN)
-          lds.u[(wv * M + m) * 64 + lane] = Vec2<U>{q[0], q[1]};
+        if ((cl[m] & (CL_IN | CL_B)) == CL_IN) lds.u[at0 + m * w] = Vec2<U>{q[0], q[1]};
       }
+    };
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+#pragma unroll
+      for (int fl = 0; fl < 2; fl++) CD::collide_raw(P, fl, raw[m][fl], rho[m][fl], fs[m][fl]);
+      if (m >= 2) update(m > 0 ? m - 1 : 0, rho[m > 1 ? m - 2 : 0], rho[m]);
+    }
+#pragma unroll
+    for (int fl = 0; fl < 2; fl++) {
+      lds.edge[par][0][fl][threadIdx.x] = rho[0][fl];
+      lds.edge[par][0][2 + fl][threadIdx.x] = fs[0][fl][4];
+      lds.edge[par][1][fl][threadIdx.x] = rho[M - 1][fl];
+      lds.edge[par][1][2 + fl][threadIdx.x] = fs[M - 1][fl][2];
+    }
+    __syncthreads();
+    // the rows below and above the group's: their moments, then the populations
+    // that come from there
+    // (a patch's outermost rows read some finite value: nothing needed depends on it)
+    const int ti = (int)threadIdx.x, below = ti >= w ? ti - w : ti, above = ti + w < 64 * kW ? ti + w : ti;
+    auto from_below = [&](int q) { return lds.edge[par][1][q][below]; };
+    auto from_above = [&](int q) { return lds.edge[par][0][q][above]; };
+    {
+      const C lo[2] = {from_below(0), from_below(1)}, hi[2] = {from_above(0), from_above(1)};
+      update(0, lo, rho[1]);
+      update(M - 1, rho[M - 2], hi);
     }
     if constexpr (BND) {
       __syncthreads();
@@ -402,6 +439,7 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
       __syncthreads();
     }
     // ---- pull: f_alpha(x, t + dt) = f*_alpha(x - c^alpha dt)
+    const C lo[2] = {from_below(2), from_below(3)}, hi[2] = {from_above(2), from_above(3)};
 #pragma unroll
     for (int m = 0; m < M; m++) {
       C f[2][5];
@@ -410,8 +448,8 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
         f[fl][0] = fs[m][fl][0];
         f[fl][1] = from_west(fs[m][fl][1]);
         f[fl][3] = from_east(fs[m][fl][3]);
-        f[fl][2] = m > 0 ? fs[m > 0 ? m - 1 : 0][fl][2] : lo[2 + fl];
-        f[fl][4] = m + 1 < M ? fs[m + 1 < M ? m + 1 : m][fl][4] : hi[2 + fl];
+        f[fl][2] = m > 0 ? fs[m > 0 ? m - 1 : 0][fl][2] : lo[fl];
+        f[fl][4] = m + 1 < M ? fs[m + 1 < M ? m + 1 : m][fl][4] : hi[fl];
       }
       if constexpr (BND) {
         // populations pulled from boundary nodes (eq. LBE_mod)
@@ -447,8 +485,7 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
   // ---- the owned nodes of t + K (u, du/dt of boundary nodes: block_boundary)
 #pragma unroll
   for (int m = 0; m < M; m++) {
-    const int r = wv * M + m;
-    if (lane >= t.ox0 && lane < t.ox1 && r >= t.oy0 && r < t.oy1 && (cl[m] & CL_IN)) {
+    if (mine(m) && (cl[m] & CL_IN)) {
       const int64_t k = node(m);
       CD::store_raw(s, a.out, 0, k, raw[m][0]);
       CD::store_raw(s, a.out, 1, k, raw[m][1]);
@@ -466,7 +503,7 @@ template <int ST, int M>
 __global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArgs a) {
   using CD = typename CodecOf<ST>::type;
   __shared__ BlockLds<CD, M> lds;
-  if (blockIdx.x == 0 && threadIdx.x == 0)
+  if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
     s.counter[a.out] = s.counter[a.in] + (unsigned long long)a.steps;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // (scalar branches)
   const int ix = tile_index(blockIdx.x, a.q);
@@ -474,37 +511,93 @@ __global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArg
   const Patch t = a.patches[ix];
   const PlateDev P = s.plates[t.plate];
   if (t.b1 <= t.b0)
-    block_march<CD, M, false>(s, a, t, P, lds);
+    block_march<CD, M, kWaves, false>(s, a, t, P, lds);
   else if (wv < kWaves - 1)
-    block_march<CD, M, true>(s, a, t, P, lds);
+    block_march<CD, M, kWaves - 1, true>(s, a, t, P, lds);
   else
     block_boundary<CD, M>(s, a, t, P, lds);
+}
+
+// (two waves per SIMD: two workgroups of four waves, or one of eight, per CU)
+template <int ST, int M, int W>
+__global__ void __launch_bounds__(64 * W, 2) k_inner(DevState s, BlockArgs a) {
+  using CD = typename CodecOf<ST>::type;
+  __shared__ EdgeLds<CD, W> lds;
+  if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
+    s.counter[a.out] = s.counter[a.in] + (unsigned long long)a.steps;
+  const int ix = tile_index(blockIdx.x, a.q);
+  if (ix >= a.n) return;
+  const Patch t = a.patches[ix];
+  const PlateDev P = s.plates[t.plate];
+  block_march<CD, M, W, false>(s, a, t, P, lds);
 }
 
 template <int ST>
 hipError_t launch_block_t(const DevState &s, const BlockArgs &a, int rows, hipStream_t st) {
   const dim3 grid(8 * a.q), th(kBlockThreads);
-  switch (rows) {
-    case 2: hipLaunchKernelGGL((k_block<ST, 2>), grid, th, 0, st, s, a); break;
-    case 4: hipLaunchKernelGGL((k_block<ST, 4>), grid, th, 0, st, s, a); break;
-    default: return hipErrorInvalidValue;
+  if (rows == 3) {
+    hipLaunchKernelGGL((k_block<ST, 3>), grid, th, 0, st, s, a);
+    return hipGetLastError();
   }
+  if (rows == 4) {
+    hipLaunchKernelGGL((k_block<ST, 4>), grid, th, 0, st, s, a);
+    return hipGetLastError();
+  }
+  if constexpr (ST != LBM_STORE_F64) {  // (FP64: past the registers)
+    if (rows == 5) {
+      hipLaunchKernelGGL((k_block<ST, 5>), grid, th, 0, st, s, a);
+      return hipGetLastError();
+    }
+    if (rows == 6) {
+      hipLaunchKernelGGL((k_block<ST, 6>), grid, th, 0, st, s, a);
+      return hipGetLastError();
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int ST>
+hipError_t launch_inner_t(const DevState &s, const BlockArgs &a, int rows, hipStream_t st) {
+  constexpr int R = block_inner_rows(ST);
+  static_assert(R % 4 == 0 && kInnerSmall % kWaves == 0, "whole rows per wave");
+  if (rows == R)
+    hipLaunchKernelGGL((k_inner<ST, R / 4, 4>), dim3(8 * a.q), dim3(256), 0, st, s, a);
+  else if (rows == kInnerSmall)
+    hipLaunchKernelGGL((k_inner<ST, kInnerSmall / kWaves, kWaves>), dim3(8 * a.q), dim3(kBlockThreads), 0,
+                       st, s, a);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_block(int storage, const DevState &s, const Patch *patches, int n, int rows,
-                        const PTask *tasks, const PGrad *grads, int in, int out, int steps,
+hipError_t launch_block(int storage, const DevState &s, const BlockWork &w, int in, int out, int steps,
                         hipStream_t st) {
-  if (n < 1 || steps < 1) return hipErrorInvalidValue;
-  const BlockArgs a{patches, tasks, grads, n, (n + 7) / 8, in, out, steps};
+  if (w.n_patches < 1 || steps < 1) return hipErrorInvalidValue;
+  const BlockArgs a{w.patches, w.tasks, w.grads, w.n_patches, (w.n_patches + 7) / 8, in, out, steps, 1};
   switch (storage) {
-    case LBM_STORE_F64: return launch_block_t<LBM_STORE_F64>(s, a, rows, st);
-    case LBM_STORE_F32: return launch_block_t<LBM_STORE_F32>(s, a, rows, st);
-    case LBM_STORE_F32DEV: return launch_block_t<LBM_STORE_F32DEV>(s, a, rows, st);
-    case LBM_STORE_F16DEV: return launch_block_t<LBM_STORE_F16DEV>(s, a, rows, st);
-    case LBM_STORE_BF16DEV: return launch_block_t<LBM_STORE_BF16DEV>(s, a, rows, st);
+    case LBM_STORE_F64: return launch_block_t<LBM_STORE_F64>(s, a, w.rows, st);
+    case LBM_STORE_F32: return launch_block_t<LBM_STORE_F32>(s, a, w.rows, st);
+    case LBM_STORE_F32DEV: return launch_block_t<LBM_STORE_F32DEV>(s, a, w.rows, st);
+    case LBM_STORE_F16DEV: return launch_block_t<LBM_STORE_F16DEV>(s, a, w.rows, st);
+    case LBM_STORE_BF16DEV: return launch_block_t<LBM_STORE_BF16DEV>(s, a, w.rows, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_inner(int storage, const DevState &s, const BlockWork &w, int in, int out, int steps,
+                        hipStream_t st) {
+  if (w.n_inner < 1 || steps < 1) return hipErrorInvalidValue;
+  // (beside a launch_block, that one counts the steps)
+  const BlockArgs a{w.inner, nullptr, nullptr, w.n_inner, (w.n_inner + 7) / 8, in, out, steps,
+                    w.n_patches < 1};
+  switch (storage) {
+    case LBM_STORE_F64: return launch_inner_t<LBM_STORE_F64>(s, a, w.inner_rows, st);
+    case LBM_STORE_F32: return launch_inner_t<LBM_STORE_F32>(s, a, w.inner_rows, st);
+    case LBM_STORE_F32DEV: return launch_inner_t<LBM_STORE_F32DEV>(s, a, w.inner_rows, st);
+    case LBM_STORE_F16DEV: return launch_inner_t<LBM_STORE_F16DEV>(s, a, w.inner_rows, st);
+    case LBM_STORE_BF16DEV: return launch_inner_t<LBM_STORE_BF16DEV>(s, a, w.inner_rows, st);
   }
   return hipErrorInvalidValue;
 }

@@ -178,7 +178,7 @@ struct lbm_ctx {
   PatchPlan plan;
   bool can_block = false;
   bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
-  Patch *d_patches = nullptr;
+  Patch *d_patches = nullptr, *d_inner = nullptr;
   PTask *d_ptasks = nullptr;
   PGrad *d_pgrads = nullptr;
   bool block = false;
@@ -1238,6 +1238,16 @@ bool overlapped_pair(const lbm_ctx *c, int64_t n) {
   return c->two && c->overlap && n > 0 && !c->dtiles.empty() && c->side != nullptr;
 }
 
+// One block pass of q steps from buffer `in` to the other one.
+hipError_t enqueue_block(lbm_ctx *c, int in, int q, hipStream_t st) {
+  const BlockWork w{c->d_patches, c->d_inner, c->d_ptasks, c->d_pgrads, (int)c->plan.patches.size(),
+                    (int)c->plan.inner.size(), c->plan.rows, c->plan.inner_rows};
+  hipError_t e = hipSuccess;
+  if (w.n_patches > 0) e = launch_block(c->storage, c->ds, w, in, in ^ 1, q, st);
+  if (e == hipSuccess && w.n_inner > 0) e = launch_inner(c->storage, c->ds, w, in, in ^ 1, q, st);
+  return e;
+}
+
 hipError_t enqueue_segment(lbm_ctx *c, int64_t s, int64_t k, int &cur, int &prev, hipStream_t st,
                            LaunchRecorder *rec) {
   auto timed = [&](int kind, hipStream_t on, auto &&fn) -> hipError_t {
@@ -1256,10 +1266,7 @@ hipError_t enqueue_segment(lbm_ctx *c, int64_t s, int64_t k, int &cur, int &prev
   if (c->block) {
     for (int64_t n = s; n < s + k && e == hipSuccess;) {
       const int q = (int)std::min<int64_t>(c->plan.K, s + k - n), in = cur;
-      e = timed(3, st, [&] {
-        return launch_block(c->storage, c->ds, c->d_patches, (int)c->plan.patches.size(),
-                            c->plan.rows, c->d_ptasks, c->d_pgrads, in, in ^ 1, q, st);
-      });
+      e = timed(3, st, [&] { return enqueue_block(c, in, q, st); });
       prev = cur;
       cur ^= 1;
       n += q;
@@ -1596,14 +1603,97 @@ lbm_status before_steps(lbm_ctx *c) {
   return LBM_OK;
 }
 
-// Steps per block pass and rows per wave of its patches.
-constexpr int kBlockSteps = 4, kBlockRows = 4;
+// A call of one step on plates whose state is past the Infinity Cache runs the
+// tile launches for its duration: there a block pass gains nothing but loads
+// and stores the patches' edges in a launch of its own (us, tiles / block: 2048^2
+// FP64 242 / 266, 8192 x 1024 with holes 500 / 644, 4096^2 823 / 943; within it
+// 1024^2 73 / 66, 512^2 42 / 32).
+struct TilesFor {
+  lbm_ctx *c;
+  bool block;
+  TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block) {
+    if (n == 1 && (double)c->n_body * bytes_per_update(c->storage) > kInfinityCacheBytes) c->block = false;
+  }
+  ~TilesFor() { c->block = block; }
+};
+
+// CUs of the GPU: workgroups of k_block that run at once.
+constexpr int kCus = 256;
+
+// Steps per pass, rows per wave of patches with boundary nodes, rows of those
+// without.
+struct BlockShape {
+  int K, rows, inner;
+};
+
+// The plan of the block pass.
+//
+// Small plates are bound by a pass's latency, about 12 + K m units with m rows
+// per wave (a unit is 0.4 us in FP32, 0.5 in FP64 without boundary nodes, 0.6 and
+// 0.85 with them: 256^2 clamped FP64, us per pass: m = 3, K = 3, 4, 5 16.9, 19.6,
+// 21.9; m = 4, K = 4, 5, 6 26.0, 28.9, 33.0), once per round of patches over the
+// CUs: the shape with the least of that per step is taken, all patches in one
+// launch.  Past two rounds throughput counts instead: patches without boundary
+// nodes go to k_inner, two to a CU, and are as large as that leaves registers
+// for.  Us per step, one launch / two: 640^2 FP32 6.3 / 9.0, 1031 x 517 FP32
+// 8.2 / 9.5, FP64 13.7 / 14.0, 1024^2 FP32 13.9 / 12.0, FP64 21.9 / 18.4.
+// K is there where the halo's growth meets the passes saved: 4096^2 with
+// a hole, K = 4, 5, 6: FP64 258, 209, 217; FP32 141, 116, 107; F32DEV 170, 138,
+// 129; F16DEV 157, 132, 149.
+bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &plan) {
+  const bool f64 = c->storage == LBM_STORE_F64, bounded = !c->bnd.empty();
+  const int R = block_inner_rows(c->storage);
+  std::vector<BlockShape> small;
+  if (!bounded)
+    small = {{6, 3, kInnerSmall}, {5, 3, kInnerSmall}, {4, 3, kInnerSmall}};
+  else if (f64)
+    small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}};
+  else
+    small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}, {6, 5, 40}, {6, 6, 48}};
+  auto cost = [&](const BlockShape &b, int64_t patches) {
+    const int m = bounded ? b.rows : b.inner / (kBlockThreads / 64);
+    return (double)((patches + kCus - 1) / kCus) * (12 + b.K * m) / b.K;
+  };
+  double best = 0;
+  const int64_t most = bounded ? 2 * kCus : kCus;
+  for (const BlockShape &b : small) {
+    // (at least as many as the body's nodes fill)
+    const int64_t own = (int64_t)(kBlockCols - 2 * b.K) * (b.inner - 2 * b.K);
+    const int64_t least = std::max<int64_t>((int64_t)v.size(), c->n_body / own);
+    if (least > most || (best > 0 && cost(b, least) >= best)) continue;
+    PatchPlan q;
+    if (!make_patch_plan(v, b.K, b.rows, b.inner, q)) continue;
+    const int64_t n = (int64_t)(q.patches.size() + q.inner.size());
+    if (n > most || (best > 0 && cost(b, n) >= best)) continue;
+    best = cost(b, n);
+    plan = std::move(q);
+  }
+  // patches without boundary nodes that k_block takes: all on small plates with
+  // some, else as many as fill its last round of CUs
+  auto fill = [&](size_t n) {
+    n = std::min(n, plan.inner.size());
+    plan.patches.insert(plan.patches.end(), plan.inner.end() - (int64_t)n, plan.inner.end());
+    plan.inner.resize(plan.inner.size() - n);
+  };
+  if (best > 0) {
+    if (bounded) fill(plan.inner.size());
+    return true;
+  }
+  const BlockShape large = f64 ? BlockShape{5, 4, R} : c->storage == LBM_STORE_F32 ? BlockShape{6, 6, R}
+                           : c->storage == LBM_STORE_F32DEV ? BlockShape{6, 5, R} : BlockShape{5, 5, R};
+  // (a plate too dense with boundary nodes for K steps may still do four)
+  if (!make_patch_plan(v, large.K, large.rows, large.inner, plan) &&
+      !make_patch_plan(v, 4, large.rows, large.inner, plan))
+    return false;
+  if (!plan.patches.empty()) fill((size_t)kCus - 1 - (plan.patches.size() + kCus - 1) % kCus);
+  return true;
+}
 
 // Cut the plates for the block pass and upload the plan (lbm_create).  False
 // if the tile launches have to do (the context stays usable): a plate whose
 // boundary nodes lie so densely that the nodes a small rectangle depends on do
 // not fit a patch, or no memory for the plan.
-bool plan_blocks(lbm_ctx *c, int K, int rows) {
+bool plan_blocks(lbm_ctx *c) {
   std::vector<PatchPlate> v(c->ph.size());
   for (size_t p = 0; p < v.size(); p++) {
     const PlateHost &h = c->ph[p];
@@ -1617,18 +1707,22 @@ bool plan_blocks(lbm_ctx *c, int K, int rows) {
     v[p].b0 = h.b0;
     v[p].nb = h.b1 - h.b0;
   }
-  if (!make_patch_plan(v, K, rows, c->plan) || c->plan.patches.empty()) return false;
+  if (!choose_plan(c, v, c->plan) || (c->plan.patches.empty() && c->plan.inner.empty())) return false;
   const PatchPlan &pl = c->plan;
-  c->d_patches = (Patch *)dev_alloc(c, pl.patches.size() * sizeof(Patch));
+  c->d_patches = (Patch *)dev_alloc(c, std::max<size_t>(1, pl.patches.size()) * sizeof(Patch));
+  c->d_inner = (Patch *)dev_alloc(c, std::max<size_t>(1, pl.inner.size()) * sizeof(Patch));
   c->d_ptasks = (PTask *)dev_alloc(c, std::max<size_t>(1, pl.tasks.size()) * sizeof(PTask));
   c->d_pgrads = (PGrad *)dev_alloc(c, std::max<size_t>(1, pl.grads.size()) * sizeof(PGrad));
   auto up = [](void *d, const void *h, size_t bytes) {
     return d && (bytes == 0 || hipMemcpy(d, h, bytes, hipMemcpyHostToDevice) == hipSuccess);
   };
   if (!up(c->d_patches, pl.patches.data(), pl.patches.size() * sizeof(Patch)) ||
+      !up(c->d_inner, pl.inner.data(), pl.inner.size() * sizeof(Patch)) ||
       !up(c->d_ptasks, pl.tasks.data(), pl.tasks.size() * sizeof(PTask)) ||
       !up(c->d_pgrads, pl.grads.data(), pl.grads.size() * sizeof(PGrad))) {
     dev_free(c, c->d_patches);
+    dev_free(c, c->d_inner);
+    c->d_inner = nullptr;
     dev_free(c, c->d_ptasks);
     dev_free(c, c->d_pgrads);
     c->d_patches = nullptr;
@@ -1992,7 +2086,7 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   build_tile_tables(c);
   if (upload_tiles(c) != LBM_OK || upload_tile_tables(c) != LBM_OK)
     return bail(LBM_E_NOMEM, c->err);
-  if (!c->variant_readings) c->block = c->can_block = plan_blocks(c, kBlockSteps, kBlockRows);
+  if (!c->variant_readings) c->block = c->can_block = plan_blocks(c);
   if (hipHostMalloc((void **)&c->h_flag, sizeof(int), hipHostMallocDefault) != hipSuccess)
     return bail(LBM_E_NOMEM, "pinned flag allocation failed");
   *c->h_flag = 0;
@@ -2070,6 +2164,7 @@ lbm_status lbm_step(lbm_ctx *c, int64_t n) {
   if (st) return st;
   st = start(c);
   if (st) return st;
+  const TilesFor tiles(c, n);
   if (n > 0) {
     st = before_steps(c);
     if (st) return st;
@@ -2109,6 +2204,7 @@ lbm_status lbm_prepare_steps(lbm_ctx *c, int64_t n) {
   if (!c->use_graphs) return LBM_OK;
   st = start(c);
   if (st) return st;
+  const TilesFor tiles(c, n);
   int64_t s = c->step;
   int cur = c->cur, prev = c->prev;
   while (n > 0) {
@@ -2712,8 +2808,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
     const double per = time_body([&](hipStream_t st2, int k) {
       hipError_t e = hipSuccess;
       for (int i = 0; i < k && e == hipSuccess; i++)
-        e = launch_block(c->storage, c->ds, c->d_patches, (int)c->plan.patches.size(), c->plan.rows,
-                         c->d_ptasks, c->d_pgrads, cur, cur ^ 1, c->plan.K, st2);
+        e = enqueue_block(c, cur, c->plan.K, st2);
       return e;
     }, true) / c->plan.K;
     if (per < best) {

@@ -22,10 +22,23 @@ hipError_t launch_deep(int storage, const DevState &s, const Tile *tiles, int nt
 // buffer `in` to the complete state in `out` (n patches of at most 8 * rows
 // rows, whose halos are for at least `steps` steps; rows: 2 or 4).  (Weak, so
 // that host-only programs link the runtime without the kernels.)
-hipError_t launch_block(int storage, const DevState &s, const Patch *patches, int n, int rows,
-                        const PTask *tasks, const PGrad *grads, int in, int out, int steps,
-                        hipStream_t stream)
-    __attribute__((weak));
+// The block pass: `steps` steps of every plate from the complete state in
+// buffer `in` to the complete state in `out`, by launch_block over `patches` (of
+// at most 8 * rows rows; rows 3 .. 6, FP64: 3, 4) and launch_inner over `inner`
+// (patches without boundary nodes, of at most inner_rows rows:
+// block_inner_rows or kInnerSmall); the patches' halos are for at least `steps`
+// steps.  Either list may be empty, not both; the two launches may overlap.
+// (Weak, so that host-only programs link the runtime without the kernels.)
+struct BlockWork {
+  const Patch *patches, *inner;
+  const PTask *tasks;
+  const PGrad *grads;
+  int n_patches, n_inner, rows, inner_rows;
+};
+hipError_t launch_block(int storage, const DevState &s, const BlockWork &w, int in, int out, int steps,
+                        hipStream_t stream) __attribute__((weak));
+hipError_t launch_inner(int storage, const DevState &s, const BlockWork &w, int in, int out, int steps,
+                        hipStream_t stream) __attribute__((weak));
 // Boundary kernel over nchunks chunks (see k_boundary): the boundary work of
 // step n - 1 on the state of t_n in buffer bc (resets and second-row pulls
 // only if do_reset).

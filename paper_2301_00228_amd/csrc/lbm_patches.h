@@ -7,7 +7,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
-#include <cstdlib>
 #include <thread>
 #include <utility>
 #include <vector>
@@ -25,57 +24,75 @@ struct PatchPlate {
   int64_t nb = 0, b0 = 0;        // their number, index of the first one
 };
 
-// What the patches of a plan are cut for: K steps, rows per wave.
+// What the patches of a plan are cut for: K steps, rows per wave of those with
+// boundary nodes, rows of those without (`inner`) at most.
 struct PatchPlan {
-  int K = 0, rows = 0;
-  std::vector<Patch> patches;
+  int K = 0, rows = 0, inner_rows = 0;
+  std::vector<Patch> patches, inner;
   std::vector<PTask> tasks;
   std::vector<PGrad> grads;
 };
 
 class PatchCutter {
  public:
-  PatchCutter(const PatchPlate &p, int K, int rows)
-      : p_(p), K_(K), hb_(rows * (kBlockThreads / 64 - 1)), hp_(rows * (kBlockThreads / 64)),
+  PatchCutter(const PatchPlate &p, int K, int rows, int inner)
+      : p_(p), K_(K), hb_(rows * (kBlockThreads / 64 - 1)), hi_(inner),
         ring_(3 * K + 4) {
     row0_.assign((size_t)p.ny + 1, 0);
     for (int64_t b = 0; b < p.nb; b++) row0_[(size_t)p.bnd[b].j + 1]++;
     for (int j = 0; j < p.ny; j++) row0_[(size_t)j + 1] += row0_[(size_t)j];
   }
 
-  // Row bands of the plate: [cut[i], cut[i + 1]); `edge`: a band along a
-  // bounded y edge.
+  // Rectangles of the plate to cut, [x0, x1) x [y0, y1), and the largest pieces
+  // to cut them into (w x h nodes; the outermost columns of a piece at a bounded
+  // x edge may be wider: we).
   struct Band {
-    int y0, y1;
-    bool edge;
+    int x0, x1, y0, y1;
+    int w, we;
   };
+  // Boundary nodes reach 2 K + 2 nodes along the boundary and K + 3 away from it;
+  // a patch without any depends on K nodes all around.
   std::vector<Band> bands() const {
     std::vector<Band> v;
-    const int mid = hp_ - 2 * K_;
-    auto even = [&](int a, int b, int h, bool edge) {
+    const int W = kBlockCols, along = 2 * K_ + 2, off = K_ + 3;
+    const int we = std::max(1, W - along);      // piece of a band along a y edge
+    const int he = std::max(1, hb_ - off);      // its rows
+    const int ws = std::max(1, W / 2 - off);    // columns along an x edge, in tall patches
+    const int hs = std::max(1, 2 * hb_ - 2 * along);  // their rows
+    auto rows = [&](int x0, int x1, int a, int b, int h, int w, int wedge) {
       const int n = (b - a + h - 1) / h;
       for (int i = 0; i < n; i++)
-        v.push_back({a + (int)((int64_t)(b - a) * i / n), a + (int)((int64_t)(b - a) * (i + 1) / n), edge});
+        v.push_back({x0, x1, a + (int)((int64_t)(b - a) * i / n), a + (int)((int64_t)(b - a) * (i + 1) / n), w, wedge});
     };
-    if (p_.py) {
-      even(0, p_.ny, mid, false);
-    } else {
-      const int he = std::max(1, hb_ - (K_ + 3));
+    int y0 = 0, y1 = p_.ny;
+    if (!p_.py) {
+      const int wedge = p_.px ? 0 : W - along;
       if (p_.ny <= 2 * he) {
-        even(0, p_.ny, p_.ny <= hb_ ? p_.ny : he, true);
-      } else {
-        v.push_back({0, he, true});
-        even(he, p_.ny - he, mid, false);
-        v.push_back({p_.ny - he, p_.ny, true});
+        rows(0, p_.nx, 0, p_.ny, p_.ny <= hb_ ? p_.ny : he, we, wedge);
+        return v;
       }
+      y0 = he;
+      y1 = p_.ny - he;
+      rows(0, p_.nx, 0, y0, he, we, wedge);
+      rows(0, p_.nx, y1, p_.ny, he, we, wedge);
     }
+    int x0 = 0, x1 = p_.nx;
+    if (!p_.px) {
+      if (p_.nx <= 2 * ws) {
+        rows(0, p_.nx, y0, y1, hs, ws, 0);
+        return v;
+      }
+      x0 = ws;
+      x1 = p_.nx - ws;
+      rows(0, x0, y0, y1, hs, ws, 0);
+      rows(x1, p_.nx, y0, y1, hs, ws, 0);
+    }
+    rows(x0, x1, y0, y1, std::max(1, hi_ - 2 * K_), std::max(1, W - 2 * K_), 0);
     return v;
   }
 
   // The patches of one band; false if some node's dependences do not fit.
   bool cut(const Band &b, PatchPlan &out) {
-    const int W = kBlockCols;
-    const int mid = std::max(1, W - 2 * (b.edge ? 2 * K_ + 2 : K_));
     bool ok = true;
     auto even = [&](int x0, int x1, int w) {
       const int n = (x1 - x0 + w - 1) / w;
@@ -83,19 +100,15 @@ class PatchCutter {
         ok = place(x0 + (int)((int64_t)(x1 - x0) * i / n), x0 + (int)((int64_t)(x1 - x0) * (i + 1) / n),
                    b.y0, b.y1, out);
     };
-    if (p_.px) {
-      even(0, p_.nx, mid);
+    const int nx = b.x1 - b.x0;
+    if (b.we > 0 && nx <= kBlockCols) {
+      even(b.x0, b.x1, nx);
+    } else if (b.we > 0 && nx > 2 * b.we) {
+      even(b.x0, b.x0 + b.we, b.we);
+      even(b.x0 + b.we, b.x1 - b.we, b.w);
+      even(b.x1 - b.we, b.x1, b.we);
     } else {
-      const int we = W - (b.edge ? 2 * K_ + 2 : K_ + 3);
-      if (p_.nx <= W) {
-        even(0, p_.nx, W);
-      } else if (p_.nx <= 2 * we) {
-        even(0, p_.nx, we);
-      } else {
-        even(0, we, we);
-        even(we, p_.nx - we, mid);
-        even(p_.nx - we, p_.nx, we);
-      }
+      even(b.x0, b.x1, b.w);
     }
     return ok;
   }
@@ -167,7 +180,7 @@ class PatchCutter {
     bool u;
   };
   PatchPlate p_;
-  int K_, hb_, hp_, ring_;
+  int K_, hb_, hi_, ring_;
   std::vector<int64_t> row0_;
   int lx_ = 0, ly_ = 0, gw_ = 0, gh_ = 0;
   std::vector<uint8_t> c_;
@@ -310,8 +323,21 @@ class PatchCutter {
     Patch t{};
     int nb = 0;
     if (!region(x0, x1, y0, y1, t.ex, t.ey, t.ew, t.eh, nb)) return true;  // nothing there
-    const int hmax = nb ? hb_ : hp_, w = x1 - x0, h = y1 - y0;
-    const int ox = t.ew - kBlockCols, oy = t.eh - hmax;
+    const int w = x1 - x0, h = y1 - y0;
+    // the shape that takes fewer pieces
+    t.w = kBlockCols;
+    int ox = t.ew - kBlockCols, oy = t.eh - (nb ? hb_ : hi_);
+    if (nb && (ox > 0 || oy > 0)) {
+      auto pieces = [](int n, int over) {  // of an axis whose excess is `over`
+        return over <= 0 ? 1 : n - over >= 1 ? (n + n - over - 1) / (n - over) : 4 * n;
+      };
+      const int ox2 = t.ew - kBlockCols / 2, oy2 = t.eh - 2 * hb_;
+      if (pieces(w, ox2) * pieces(h, oy2) < pieces(w, ox) * pieces(h, oy)) {
+        t.w = kBlockCols / 2;
+        ox = ox2;
+        oy = oy2;
+      }
+    }
     if (ox > 0 || oy > 0 || nb > kBlockTasks || (nb && gradients(t) > kBlockGrads)) {
       // into as many equal parts as leave the excess out, along the axis in excess
       const bool sx = ox > 0 ? true : oy > 0 ? false : w >= h;
@@ -338,7 +364,7 @@ class PatchCutter {
     for (int q = 0; q < (nb ? (int)g_.size() : 0); q++) {
       const int i = g_[(size_t)q].first, j = g_[(size_t)q].second;
       PGrad G{};
-      G.l = (uint16_t)((j - t.ey) * kBlockCols + (i - t.ex));
+      G.l = (uint16_t)((j - t.ey) * t.w + (i - t.ex));
       G.code = (uint16_t)(code(i, j, 0) | (code(i, j, 1) << 3));
       G.task = q < nb ? (int16_t)q : (int16_t)-1;
       out.grads.push_back(G);
@@ -366,10 +392,11 @@ class PatchCutter {
   }
 };
 
-// The plan for K steps with `rows` rows per wave over all plates; false if
-// some plate cannot be cut (a node's dependences exceed a patch).  Bands are
+// The plan for K steps with `rows` rows per wave (patches without boundary
+// nodes: `inner` rows at most) over all plates; false if some plate cannot be cut (a node's dependences exceed a patch).  Bands are
 // cut by several host threads; the result does not depend on their number.
-inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int rows, PatchPlan &plan) {
+inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int rows, int inner,
+                            PatchPlan &plan) {
   struct Job {
     int plate;
     PatchCutter::Band band;
@@ -379,7 +406,7 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
   std::vector<Job> jobs;
   int64_t nodes = 0;
   for (size_t p = 0; p < plates.size(); p++) {
-    PatchCutter c(plates[p], K, rows);
+    PatchCutter c(plates[p], K, rows, inner);
     for (const auto &b : c.bands()) jobs.push_back(Job{(int)p, b, {}, false});
     nodes += (int64_t)plates[p].nx * plates[p].ny;
   }
@@ -392,7 +419,7 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
       for (size_t i = next++; i < jobs.size() && !failed; i = next++) {
         if (have != jobs[i].plate) {
           cutter.clear();
-          cutter.emplace_back(plates[(size_t)jobs[i].plate], K, rows);
+          cutter.emplace_back(plates[(size_t)jobs[i].plate], K, rows, inner);
           have = jobs[i].plate;
         }
         jobs[i].ok = cutter[0].cut(jobs[i].band, jobs[i].out);
@@ -416,7 +443,9 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
   if (failed) return false;
   plan.K = K;
   plan.rows = rows;
+  plan.inner_rows = inner;
   plan.patches.clear();
+  plan.inner.clear();
   plan.tasks.clear();
   plan.grads.clear();
   for (Job &j : jobs) {
@@ -426,7 +455,7 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
       t.b1 += tb;
       t.g0 += gb;
       t.g1 += gb;
-      plan.patches.push_back(t);
+      (t.b1 > t.b0 ? plan.patches : plan.inner).push_back(t);
     }
     plan.tasks.insert(plan.tasks.end(), j.out.tasks.begin(), j.out.tasks.end());
     plan.grads.insert(plan.grads.end(), j.out.grads.begin(), j.out.grads.end());

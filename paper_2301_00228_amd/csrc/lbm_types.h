@@ -230,19 +230,20 @@ struct Prologue {
   int enabled;
 };
 
-// One workgroup of the block pass (k_block): the patch of ew x eh nodes from
-// (ex, ey) (not wrapped: may be negative or past the plate on a periodic
+// One workgroup of the block pass (k_block, k_inner): the patch of ew x eh nodes
+// from (ex, ey) (not wrapped: may be negative or past the plate on a periodic
 // axis) whose nodes [ox0, ox1) x [oy0, oy1) (patch coordinates) it owns, its
 // boundary tasks [b0, b1) (none: a patch of interior nodes) and the gradient
-// nodes [g0, g1) they read.
+// nodes [g0, g1) they read.  w: columns of its layout, kBlockCols, or half of
+// them in a tall patch (a wave then holds two row groups side by side).
 struct Patch {
   int32_t plate, ex, ey, ew, eh;
   int32_t ox0, ox1, oy0, oy1;
   int32_t b0, b1, g0, g1;
-  int32_t pad;
+  int32_t w;
 };
 
-// A boundary node of a patch: its record, its place in the patch (row * 64 +
+// A boundary node of a patch: its record, its place in the patch (row * w +
 // column), whether the patch owns it, and the gradient nodes (relative to the
 // patch's) of the node and of its E, N, W, S neighbours (-1: not in the body).
 struct PTask {
@@ -270,11 +271,21 @@ struct BlockArgs {
   int n, q;       // patches, patches per XCD
   int in, out;    // state buffers of t and t + steps
   int steps;
+  int count;      // set the step counter of `out`
 };
 
 constexpr int kBlockThreads = 512;  // threads of a block-pass workgroup
 constexpr int kBlockCols = 64;      // columns of a patch at most
 constexpr int kBlockTasks = 256;    // boundary nodes of a patch at most
 constexpr int kBlockGrads = kBlockThreads;  // gradient nodes of a patch at most
+
+// Rows of a patch of k_inner at most (a multiple of its four waves): what four
+// waves can hold in 256 registers per lane, so that two patches share a CU.
+constexpr int block_inner_rows(int storage) {
+  return storage == LBM_STORE_F64 ? 28 : storage == LBM_STORE_F32 ? 48 : storage == LBM_STORE_BF16DEV ? 36 : 40;
+}
+// The smaller patches of k_inner on small plates without boundary nodes (eight
+// waves, two rows each).
+constexpr int kInnerSmall = 16;
 
 }  // namespace lbm

@@ -4,7 +4,8 @@
 // come from the library's host source, whose kernel launchers are stubs.
 //
 // stdin: n_plates, then per plate: nx ny periodic_x periodic_y, ny rows of
-//        nx 0/1; n_plans, then per plan: steps rows
+//        nx 0/1; n_plans, then per plan: steps, rows per wave, rows
+//        of a patch without boundary nodes
 // stdout: per plan "patches P bounded B tasks T violations V"
 #include <cstdio>
 #include <iostream>
@@ -69,14 +70,16 @@ int main() {
   int nplans, total = 0;
   std::cin >> nplans;
   for (int q = 0; q < nplans; q++) {
-    int K, rows, bad = 0, bounded = 0;
-    std::cin >> K >> rows;
+    int K, rows, inner, bad = 0, bounded = 0;
+    std::cin >> K >> rows >> inner;
     PatchPlan plan;
-    if (!make_patch_plan(pp, K, rows, plan)) {
-      printf("plan %d %d: not cut\n", K, rows);
+    if (!make_patch_plan(pp, K, rows, inner, plan)) {
+      printf("plan %d %d %d: not cut\n", K, rows, inner);
       total++;
       continue;
     }
+    const size_t nb = plan.patches.size();  // (then the patches without boundary nodes)
+    plan.patches.insert(plan.patches.end(), plan.inner.begin(), plan.inner.end());
     auto report = [&](const char *what, size_t i) {
       if (bad++ < 10) {
         const Patch &t = plan.patches[i];
@@ -91,8 +94,10 @@ int main() {
       const PlateHost &h = ph[t.plate];
       const bool has = t.b1 > t.b0;
       bounded += has;
-      const int hmax = rows * (kBlockThreads / 64 - (has ? 1 : 0));
-      if (t.ew < 1 || t.ew > kBlockCols || t.eh < 1 || t.eh > hmax) report("size", i);
+      if (has != (i < nb)) report("list", i);
+      const int hmax = has ? rows * (kBlockThreads / 64 - 1) * (kBlockCols / t.w) : inner;
+      if (t.w != kBlockCols && (t.w != kBlockCols / 2 || !has)) report("shape", i);
+      if (t.ew < 1 || t.ew > t.w || t.eh < 1 || t.eh > hmax) report("size", i);
       if (t.ox0 < 0 || t.ox1 > t.ew || t.ox0 >= t.ox1 || t.oy0 < 0 || t.oy1 > t.eh || t.oy0 >= t.oy1)
         report("owned rectangle", i);
       if (t.b1 - t.b0 > kBlockTasks) report("tasks", i);
@@ -124,7 +129,7 @@ int main() {
           const BndNode &B = bnd[t.plate][(size_t)(T.bnd - pp[t.plate].b0)];
           const int x = ((t.ex + a) % h.nx + h.nx) % h.nx, y = ((t.ey + b) % h.ny + h.ny) % h.ny;
           const bool own = a >= t.ox0 && a < t.ox1 && b >= t.oy0 && b < t.oy1;
-          if (T.l != b * kBlockCols + a || B.i != x || B.j != y || (T.own != 0) != own) report("task", i);
+          if (T.l != b * t.w + a || B.i != x || B.j != y || (T.own != 0) != own) report("task", i);
           const int di[5] = {0, 1, 0, -1, 0}, dj[5] = {0, 0, 1, 0, -1};
           for (int d = 0; d < 5; d++) {
             const bool in = (cls(a + di[d], b + dj[d]) & CL_IN) != 0;
@@ -136,7 +141,7 @@ int main() {
             }
             const PGrad &G = plan.grads[(size_t)(t.g0 + T.g[d])];
             const int xx = ((x + di[d]) % h.nx + h.nx) % h.nx, yy = ((y + dj[d]) % h.ny + h.ny) % h.ny;
-            if (G.l != (b + dj[d]) * kBlockCols + a + di[d]) report("gradient place", i);
+            if (G.l != (b + dj[d]) * t.w + a + di[d]) report("gradient place", i);
             if (G.code != (fd_code_host(h, xx, yy, 0) | (fd_code_host(h, xx, yy, 1) << 3)))
               report("stencil code", i);
             if (d == 0 && G.task != at - t.b0) report("gradient's task", i);
@@ -146,7 +151,7 @@ int main() {
       if (at != t.b1) report("task count", i);
       for (int g = t.g0; g < t.g1; g++) {
         const PGrad &G = plan.grads[(size_t)g];
-        const uint8_t c = cls(G.l % kBlockCols, G.l / kBlockCols);
+        const uint8_t c = cls(G.l % t.w, G.l / t.w);
         if (!(c & CL_IN) || (G.task >= 0) != ((c & CL_B) != 0)) report("gradient node", i);
       }
       // K steps of validity: a value is valid if everything it is computed

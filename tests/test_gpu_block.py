@@ -69,6 +69,22 @@ def test_periodic_axes_bitwise(nx, ny, per):
     same(cases, "f64", (9, 30))
 
 
+@pytest.mark.parametrize("storage", STORAGES)
+def test_every_shape_of_patches_bitwise(storage):
+    # one launch with 3 to 6 rows per wave; two launches, few edges and many;
+    # without boundary nodes, small and large
+    many = I.plate_batch(count=4, side_lo=500, side_hi=900, steps=0)
+    for cases in ([clamped(300, 280)], [clamped(500, 515)], [clamped(645, 600)], [clamped(1031, 517)],
+                  [I.plate_with_hole(n=1100, radius=130, sigma=8.0, steps=0)], many):
+        same(cases, storage, (7, 52))
+    # (single steps of a state past the Infinity Cache: the tile launches)
+    same([clamped(2100, 1000), clamped(2000, 900)], storage, (1, 1, 6, 1, 49, 1))
+    for nx, ny in ((190, 131), (820, 803)):
+        c = clamped(nx, ny, a0_phi=0.99)
+        c.periodic, c.bcs, c.sync_every = (True, True), [], 0
+        same([c], storage, (7, 52))
+
+
 def test_strip_with_holes_matches_the_oracle():
     case = I.strip_with_holes(nx=500, ny=120, sigma=6.0, pulses=3, steps=103, seed_index=7)
     ref, _ = run_case(case)

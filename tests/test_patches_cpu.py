@@ -24,8 +24,9 @@ SOURCES = [os.path.join(ROOT, "tests", "patches_harness.cpp"),
            os.path.join(ROOT, "tests", "tiles_harness.cpp"),
            os.path.join(ROOT, "include", "lbm.h")]
 SOURCES += [os.path.join(CSRC, f) for f in ("lbm_host.cpp", "lbm_types.h", "lbm_kernels.h", "lbm_patches.h")]
-# steps, rows per wave
-PLANS = [(4, 4), (2, 2), (1, 2), (3, 4), (2, 4)]
+# steps, rows per wave, rows of a patch without boundary nodes
+PLANS = [(4, 4, 32), (2, 2, 16), (1, 2, 8), (3, 4, 28), (5, 3, 24), (5, 4, 28), (5, 5, 40), (6, 3, 16), (6, 5, 40),
+         (6, 6, 48)]
 
 
 @pytest.fixture(scope="module")
@@ -52,7 +53,7 @@ def check(exe, plates, plans):
         lines.append(f"{nx} {ny} {int(px)} {int(py)}")
         lines.extend(" ".join(str(int(v)) for v in row) for row in mask)
     lines.append(str(len(plans)))
-    lines += [f"{k} {r}" for k, r in plans]
+    lines += [" ".join(str(v) for v in p) for p in plans]
     r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=300)
     print(r.stdout)
     assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-2000:])
@@ -93,4 +94,4 @@ def test_bodies_that_are_mostly_boundary(harness):
         b[o:o + 2, :] = 1
     for o in range(0, 48, 8):
         b[:, o:o + 2] = 1
-    check(harness, [(a, (False, False)), (b, (False, False))], [(2, 2), (1, 2), (2, 4)])
+    check(harness, [(a, (False, False)), (b, (False, False))], [(2, 2, 16), (1, 2, 8), (2, 4, 32)])
