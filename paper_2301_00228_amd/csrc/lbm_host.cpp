@@ -156,7 +156,6 @@ struct lbm_ctx {
   SecNode *d_sec = nullptr;
   LoadTable *d_loads = nullptr;
   unsigned long long *d_counter = nullptr;
-  int *d_flag = nullptr;
   uint8_t *d_cls = nullptr;
   double *d_scratch = nullptr;
   size_t scratch_bytes = 0;
@@ -190,7 +189,9 @@ struct lbm_ctx {
   // Captured step graphs, keyed by what the launch sequence of k steps from
   // step s depends on: k, s modulo lcm(l, 2) (synchronization points, step
   // parity), s == 0 (the first step of a run differs) and the buffers (cur,
-  // prev) at s.  Least recently used ones are dropped beyond kMaxGraphs.
+  // prev) at s; block passes depend on less, so that calls of few steps find
+  // their graphs again at other steps (see graph_for).  The less recently used
+  // half is dropped beyond kMaxGraphs.
   struct GraphEntry {
     int64_t k = 0, phase = 0;
     bool first = false;
@@ -204,7 +205,9 @@ struct lbm_ctx {
   int64_t steps_in_graphs = 0;  // steps run by graph replays so far
   int64_t syncs_done = 0;       // synchronization steps enqueued so far
 
-  int *h_flag = nullptr;
+  // Set by kernels that meet a non-finite or blown-up displacement: in pinned
+  // host memory, so that a call leaves no copy behind its launches.
+  volatile int *h_flag = nullptr;
   hipEvent_t flag_ev = nullptr;
   bool flag_pending = false;
   bool nonfinite = false;
@@ -285,6 +288,7 @@ void dev_free_all(lbm_ctx *c) {
 }
 
 void drop_graph(lbm_ctx *c) {
+  if (!c->graphs.empty()) (void)hipStreamSynchronize(c->stream);  // (none in flight)
   for (auto &g : c->graphs) {
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
     if (g.graph) (void)hipGraphDestroy(g.graph);
@@ -1415,7 +1419,7 @@ int64_t graph_period(const lbm_ctx *c) {
   return 0;  // no period found: graphs of at most kMaxGraphSteps steps
 }
 
-constexpr size_t kMaxGraphs = 8;
+constexpr size_t kMaxGraphs = 32;
 constexpr int64_t kMaxGraphSteps = 256;
 
 // Period of the launch sequence's dependence on the starting step.
@@ -1435,11 +1439,15 @@ int64_t graph_chunk(const lbm_ctx *c, int64_t s, int64_t n) {
 // The captured graph of steps [s, s + k) from buffers (cur, prev), from the
 // cache or captured now.
 lbm_status graph_for(lbm_ctx *c, int64_t s, int64_t k, int cur, int prev, hipGraphExec_t *out) {
-  const int64_t phase = s % phase_period(c);
-  const bool first = s == 0;
-  const int cur0 = cur, prev0 = prev;
+  // (block passes: steps to the first synchronization, k + 1 if past the run's end;
+  // nothing else of s, and not prev)
+  const int64_t phase = !c->block ? s % phase_period(c)
+                        : c->sync_every > 0 ? std::min<int64_t>(k + 1, c->sync_every - s % c->sync_every)
+                                            : 0;
+  const bool first = !c->block && s == 0;
+  const int cur0 = cur, prev0 = c->block ? -1 : prev;
   for (auto &g : c->graphs)
-    if (g.k == k && g.phase == phase && g.first == first && g.cur == cur && g.prev == prev) {
+    if (g.k == k && g.phase == phase && g.first == first && g.cur == cur0 && g.prev == prev0) {
       g.used = ++c->graph_clock;
       *out = g.exec;
       return LBM_OK;
@@ -1468,13 +1476,16 @@ lbm_status graph_for(lbm_ctx *c, int64_t s, int64_t k, int cur, int prev, hipGra
     return hip_fail(c, e, "graph instantiate");
   }
   if (c->graphs.size() >= kMaxGraphs) {
-    auto lru = std::min_element(c->graphs.begin(), c->graphs.end(),
-                                [](const lbm_ctx::GraphEntry &a, const lbm_ctx::GraphEntry &b) {
-                                  return a.used < b.used;
-                                });
-    (void)hipGraphExecDestroy(lru->exec);
-    (void)hipGraphDestroy(lru->graph);
-    c->graphs.erase(lru);
+    // (the older half at once: a graph is destroyed only after its last launch,
+    // which has to be waited for)
+    (void)hipStreamSynchronize(c->stream);
+    std::sort(c->graphs.begin(), c->graphs.end(),
+              [](const lbm_ctx::GraphEntry &x, const lbm_ctx::GraphEntry &y) { return x.used > y.used; });
+    while (c->graphs.size() > kMaxGraphs / 2) {
+      (void)hipGraphExecDestroy(c->graphs.back().exec);
+      (void)hipGraphDestroy(c->graphs.back().graph);
+      c->graphs.pop_back();
+    }
   }
   lbm_ctx::GraphEntry ent;
   ent.k = k;
@@ -1807,7 +1818,7 @@ void lbm_destroy(lbm_ctx *c) {
   }
 
   if (c->flag_ev) (void)hipEventDestroy(c->flag_ev);
-  if (c->h_flag) (void)hipHostFree(c->h_flag);
+  if (c->h_flag) (void)hipHostFree((void *)c->h_flag);
   dev_free_all(c);
   delete c;
 }
@@ -1994,7 +2005,6 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   c->d_sec = (SecNode *)dev_alloc(c, std::max<size_t>(1, c->sec.size()) * sizeof(SecNode));
   c->d_loads = (LoadTable *)dev_alloc(c, (size_t)n_plates * kMaxLoadsPerPlate * sizeof(LoadTable));
   c->d_counter = (unsigned long long *)dev_alloc(c, 256);
-  c->d_flag = (int *)(((char *)c->d_counter) + 64);
   if (!c->d_cls || !c->d_plates || !c->d_bnd || !c->d_sec || !c->d_loads || !c->d_counter)
     return bail(LBM_E_NOMEM, "metadata allocation failed");
   c->ds.cls = c->d_cls;
@@ -2003,7 +2013,13 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   c->ds.bnd = c->d_bnd;
   c->ds.sec = c->d_sec;
   c->ds.counter = c->d_counter;
-  c->ds.flag = c->d_flag;
+  int *hf = nullptr;
+  if (hipHostMalloc((void **)&hf, sizeof(int), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
+    return bail(LBM_E_NOMEM, "pinned flag allocation failed");
+  c->h_flag = hf;
+  *c->h_flag = 0;
+  if (hipHostGetDevicePointer((void **)&c->ds.flag, hf, 0) != hipSuccess)
+    return bail(LBM_E_DEVICE, "flag address");
 
   hipError_t e;
   if ((e = hipMemset(c->d_counter, 0, 256)) != hipSuccess) return bail(LBM_E_DEVICE, "memset");
@@ -2087,9 +2103,6 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   if (upload_tiles(c) != LBM_OK || upload_tile_tables(c) != LBM_OK)
     return bail(LBM_E_NOMEM, c->err);
   if (!c->variant_readings) c->block = c->can_block = plan_blocks(c);
-  if (hipHostMalloc((void **)&c->h_flag, sizeof(int), hipHostMallocDefault) != hipSuccess)
-    return bail(LBM_E_NOMEM, "pinned flag allocation failed");
-  *c->h_flag = 0;
   if (hipEventCreateWithFlags(&c->flag_ev, hipEventDisableTiming) != hipSuccess)
     return bail(LBM_E_DEVICE, "event creation failed");
   if (hipDeviceSynchronize() != hipSuccess) return bail(LBM_E_DEVICE, "synchronize");
@@ -2190,8 +2203,6 @@ lbm_status lbm_step(lbm_ctx *c, int64_t n) {
     c->step += k;
     n -= k;
   }
-  HIP_TRY(c, hipMemcpyAsync(c->h_flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost, c->stream),
-          "flag copy");
   HIP_TRY(c, hipEventRecord(c->flag_ev, c->stream), "flag event");
   c->flag_pending = true;
   return LBM_OK;
@@ -2253,9 +2264,7 @@ lbm_status lbm_fields(lbm_ctx *c, int32_t plate, double *e, double *w, double *u
   if (w) HIP_TRY(c, hipMemcpy(w, dw, n * sizeof(double), hipMemcpyDeviceToHost), "copy omega");
   if (u) HIP_TRY(c, hipMemcpy(u, du, 2 * n * sizeof(double), hipMemcpyDeviceToHost), "copy u");
   if (v) HIP_TRY(c, hipMemcpy(v, dv, 2 * n * sizeof(double), hipMemcpyDeviceToHost), "copy v");
-  int flag = 0;
-  HIP_TRY(c, hipMemcpy(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost), "copy flag");
-  if (flag) c->nonfinite = true;
+  if (*c->h_flag) c->nonfinite = true;
   return check_flag(c, true);
 }
 
@@ -2291,9 +2300,7 @@ lbm_status lbm_fields_noalloc(lbm_ctx *c, int32_t plate, double *e, double *w, d
   if (w) HIP_TRY(c, hipMemcpy(w, dw, n * sizeof(double), hipMemcpyDeviceToHost), "copy omega");
   if (u) HIP_TRY(c, hipMemcpy(u, du, 2 * n * sizeof(double), hipMemcpyDeviceToHost), "copy u");
   if (v) HIP_TRY(c, hipMemcpy(v, dv, 2 * n * sizeof(double), hipMemcpyDeviceToHost), "copy v");
-  int flag = 0;
-  HIP_TRY(c, hipMemcpy(&flag, c->d_flag, sizeof(int), hipMemcpyDeviceToHost), "copy flag");
-  if (flag) c->nonfinite = true;
+  if (*c->h_flag) c->nonfinite = true;
   return check_flag(c, true);
 }
 
