@@ -176,6 +176,7 @@ struct lbm_ctx {
   // asks for several steps per pass; not under one with steps = 1.
   PatchPlan plan;
   bool can_block = false;
+  bool tables = false;  // the tiles' prologue lists are in place (see ensure_tables)
   bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
   Patch *d_patches = nullptr, *d_inner = nullptr;
   PTask *d_ptasks = nullptr;
@@ -1120,13 +1121,40 @@ lbm_status upload_tiles(lbm_ctx *c) {
   return upload_tile_list(c, c->etiles, c->d_etiles, c->etiles_cap);
 }
 
+// The state is past the Infinity Cache (a pass over it moves more than that).
+bool past_cache(const lbm_ctx *c) {
+  return (double)c->n_body * bytes_per_update(c->storage) > kInfinityCacheBytes;
+}
+
+// The tiles' prologue lists, which only the tile launches read: built when they
+// first run (c->tables), since a context that takes block passes may never need
+// them (1.9 ms of host work at 1024^2); at once where calls of one step do.
+lbm_status ensure_tables(lbm_ctx *c) {
+  if (c->tables) return LBM_OK;
+  HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");  // (launches that read the tiles)
+  build_tile_tables(c);
+  lbm_status st = upload_tiles(c);
+  if (st) return st;
+  st = upload_tile_tables(c);
+  if (st) return st;
+  c->tables = true;
+  return LBM_OK;
+}
+
+// The tiles after a change of the tiling.
+lbm_status new_tiles(lbm_ctx *c) {
+  c->tables = false;
+  build_tiles(c);
+  return c->block && !past_cache(c) ? upload_tiles(c) : ensure_tables(c);
+}
+
 lbm_status upload_boundary(lbm_ctx *c) {
   if (!c->bnd.empty())
     HIP_TRY(c, hipMemcpy(c->d_bnd, c->bnd.data(), c->bnd.size() * sizeof(BndNode),
                          hipMemcpyHostToDevice),
             "boundary upload");
   for (size_t t = 0; t < c->btasks.size(); t++) c->btasks[t].b = c->bnd[(size_t)c->btask_bnd[t]];
-  {
+  if (c->tables) {
     lbm_status st = upload_tile_tables(c);
     if (st) return st;
   }
@@ -1609,7 +1637,10 @@ lbm_status ensure_ahead(lbm_ctx *c) {
 // What has to be in place before steps are enqueued from the current state;
 // a block pass leaves no boundary accelerations for the next step.
 lbm_status before_steps(lbm_ctx *c) {
-  if (!c->block) return ensure_ahead(c);
+  if (!c->block) {
+    lbm_status st = ensure_tables(c);
+    return st ? st : ensure_ahead(c);
+  }
   c->ahead = false;
   return LBM_OK;
 }
@@ -1623,7 +1654,7 @@ struct TilesFor {
   lbm_ctx *c;
   bool block;
   TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block) {
-    if (n == 1 && (double)c->n_body * bytes_per_update(c->storage) > kInfinityCacheBytes) c->block = false;
+    if (n == 1 && past_cache(c)) c->block = false;
   }
   ~TilesFor() { c->block = block; }
 };
@@ -1720,27 +1751,28 @@ bool plan_blocks(lbm_ctx *c) {
   }
   if (!choose_plan(c, v, c->plan) || (c->plan.patches.empty() && c->plan.inner.empty())) return false;
   const PatchPlan &pl = c->plan;
-  c->d_patches = (Patch *)dev_alloc(c, std::max<size_t>(1, pl.patches.size()) * sizeof(Patch));
-  c->d_inner = (Patch *)dev_alloc(c, std::max<size_t>(1, pl.inner.size()) * sizeof(Patch));
-  c->d_ptasks = (PTask *)dev_alloc(c, std::max<size_t>(1, pl.tasks.size()) * sizeof(PTask));
-  c->d_pgrads = (PGrad *)dev_alloc(c, std::max<size_t>(1, pl.grads.size()) * sizeof(PGrad));
-  auto up = [](void *d, const void *h, size_t bytes) {
-    return d && (bytes == 0 || hipMemcpy(d, h, bytes, hipMemcpyHostToDevice) == hipSuccess);
+  // (one allocation and one copy)
+  std::vector<char> blob;
+  auto add = [&](const void *h, size_t bytes) {
+    const size_t at = (blob.size() + 255) / 256 * 256;
+    blob.resize(at + bytes);
+    if (bytes) memcpy(blob.data() + at, h, bytes);
+    return at;
   };
-  if (!up(c->d_patches, pl.patches.data(), pl.patches.size() * sizeof(Patch)) ||
-      !up(c->d_inner, pl.inner.data(), pl.inner.size() * sizeof(Patch)) ||
-      !up(c->d_ptasks, pl.tasks.data(), pl.tasks.size() * sizeof(PTask)) ||
-      !up(c->d_pgrads, pl.grads.data(), pl.grads.size() * sizeof(PGrad))) {
-    dev_free(c, c->d_patches);
-    dev_free(c, c->d_inner);
-    c->d_inner = nullptr;
-    dev_free(c, c->d_ptasks);
-    dev_free(c, c->d_pgrads);
-    c->d_patches = nullptr;
-    c->d_ptasks = nullptr;
-    c->d_pgrads = nullptr;
+  const size_t a = add(pl.patches.data(), pl.patches.size() * sizeof(Patch));
+  const size_t b = add(pl.inner.data(), pl.inner.size() * sizeof(Patch));
+  const size_t t = add(pl.tasks.data(), pl.tasks.size() * sizeof(PTask));
+  const size_t g = add(pl.grads.data(), pl.grads.size() * sizeof(PGrad));
+  char *d = (char *)dev_alloc(c, blob.size());
+  if (!d) return false;
+  if (hipMemcpy(d, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    dev_free(c, d);
     return false;
   }
+  c->d_patches = (Patch *)(d + a);
+  c->d_inner = (Patch *)(d + b);
+  c->d_ptasks = (PTask *)(d + t);
+  c->d_pgrads = (PGrad *)(d + g);
   return true;
 }
 
@@ -2098,11 +2130,8 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   c->rows = 8;
   c->edge_rows = 2;
   c->align = c->n_body < ((int64_t)4 << 20) ? 0 : 16;
-  build_tiles(c);
-  build_tile_tables(c);
-  if (upload_tiles(c) != LBM_OK || upload_tile_tables(c) != LBM_OK)
-    return bail(LBM_E_NOMEM, c->err);
   if (!c->variant_readings) c->block = c->can_block = plan_blocks(c);
+  if (new_tiles(c) != LBM_OK) return bail(LBM_E_NOMEM, c->err);
   if (hipEventCreateWithFlags(&c->flag_ev, hipEventDisableTiming) != hipSuccess)
     return bail(LBM_E_DEVICE, "event creation failed");
   if (hipDeviceSynchronize() != hipSuccess) return bail(LBM_E_DEVICE, "synchronize");
@@ -2216,6 +2245,10 @@ lbm_status lbm_prepare_steps(lbm_ctx *c, int64_t n) {
   st = start(c);
   if (st) return st;
   const TilesFor tiles(c, n);
+  if (!c->block) {
+    st = ensure_tables(c);
+    if (st) return st;
+  }
   int64_t s = c->step;
   int cur = c->cur, prev = c->prev;
   while (n > 0) {
@@ -2384,11 +2417,7 @@ lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
       return st3;
     }
   }
-  build_tiles(c);
-  build_tile_tables(c);
-  lbm_status st = upload_tiles(c);
-  if (st) return st;
-  st = upload_tile_tables(c);
+  lbm_status st = new_tiles(c);
   if (st) return st;
   drop_graph(c);
   return LBM_OK;
@@ -2406,11 +2435,7 @@ lbm_status lbm_use_overlap(lbm_ctx *c, int32_t enable) {
   HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
   c->overlap = enable != 0;
   // (the frame tiles are cut shorter with overlapped pairs)
-  build_tiles(c);
-  build_tile_tables(c);
-  lbm_status st = upload_tiles(c);
-  if (st) return st;
-  st = upload_tile_tables(c);
+  lbm_status st = new_tiles(c);
   if (st) return st;
   drop_graph(c);
   return LBM_OK;
@@ -2493,7 +2518,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   const bool syncs_now = c->sync_every > 0 && c->step % c->sync_every == 0;
   const bool fresh = !c->ahead;  // (a block pass leaves no populations of t_{n-1} either)
   c->block = false;
-  st = ensure_ahead(c);
+  st = before_steps(c);
   if (st) return st;
   if (fresh || c->step == 0 || (syncs_now && c->sync_every > 1) || c->prev == 2) {
     HIP_TRY(c, enqueue_segment(c, c->step, 1, c->cur, c->prev, c->stream, nullptr),
@@ -2846,11 +2871,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   c->block = use_block;
   c->tiled = true;
   if ((!c->two || c->block) && !had_third) release_third(c);
-  build_tiles(c);
-  build_tile_tables(c);
-  st = upload_tiles(c);
-  if (st) return st;
-  st = upload_tile_tables(c);
+  st = new_tiles(c);
   if (st) return st;
   drop_graph(c);
   if (best_ms) *best_ms = best;

@@ -126,18 +126,9 @@ class PatchCutter {
   // the neighbours' fields of t + j - 1, at a boundary node u of t + j - 1 on
   // the stencils of the node and its body neighbours.
   bool region(int x0, int x1, int y0, int y1, int &ex, int &ey, int &ew, int &eh, int &nb) {
-    lx_ = x0 - ring_;
-    ly_ = y0 - ring_;
-    gw_ = x1 - x0 + 2 * ring_;
-    gh_ = y1 - y0 + 2 * ring_;
-    load_classes();
-    bool body = false, near = false;
-    for (int j = y0; j < y1 && !body; j++)
-      for (int i = x0; i < x1 && !body; i++) body = (at(i, j) & CL_IN) != 0;
-    if (!body) return false;
-    for (int j = y0 - K_; j < y1 + K_ && !near; j++)
-      for (int i = x0 - K_; i < x1 + K_ && !near; i++) near = (at(i, j) & CL_B) != 0;
-    if (!near) {
+    if (!any_boundary(x0 - K_, x1 + K_, y0 - K_, y1 + K_)) {
+      // (the body begins and ends at boundary nodes)
+      if (!(p_.cls[(size_t)y0 * p_.nx + x0] & CL_IN)) return false;
       ex = x0 - K_;
       ey = y0 - K_;
       ew = x1 - x0 + 2 * K_;
@@ -145,16 +136,32 @@ class PatchCutter {
       nb = 0;
       return true;
     }
+    lx_ = x0 - ring_;
+    ly_ = y0 - ring_;
+    gw_ = x1 - x0 + 2 * ring_;
+    gh_ = y1 - y0 + 2 * ring_;
+    load_classes();
     lf_.assign(c_.size(), -1);
     lu_.assign(c_.size(), -1);
-    queue_.assign((size_t)K_ + 1, {});
+    queue_.resize((size_t)K_ + 1);
+    for (auto &q : queue_) q.clear();
     minx_ = miny_ = INT32_MAX;
     maxx_ = maxy_ = INT32_MIN;
+    // the rectangle's own nodes; what a node not at its border and not next to
+    // the boundary depends on is among them
     for (int j = y0; j < y1; j++)
       for (int i = x0; i < x1; i++) {
-        need_f(i, j, K_);
-        need_u(i, j, K_);
+        const int k = id(i, j);
+        const uint8_t c = c_[(size_t)k];
+        if (!(c & CL_IN)) continue;
+        extend(i, j);
+        lf_[(size_t)k] = lu_[(size_t)k] = (int8_t)K_;
+        if ((c & (CL_B | CL_S)) || j == y0 || j == y1 - 1 || i == x0 || i == x1 - 1) {
+          queue_[(size_t)K_].push_back({k, false});
+          queue_[(size_t)K_].push_back({k, true});
+        }
       }
+    if (maxx_ < minx_) return false;
     for (int l = K_; l >= 0; l--)
       for (size_t q = 0; q < queue_[(size_t)l].size(); q++) {  // (grows while it is walked)
         const Item it = queue_[(size_t)l][q];
@@ -211,6 +218,27 @@ class PatchCutter {
         if (b > a) std::copy(src + a, src + b, dst + (a - lx_));
       }
     }
+  }
+  // Some boundary node in [x0, x1) x [y0, y1) (not wrapped)?
+  bool any_boundary(int x0, int x1, int y0, int y1) const {
+    for (int j = y0; j < y1; j++) {
+      int y = j;
+      if (p_.py)
+        y = ((j % p_.ny) + p_.ny) % p_.ny;
+      else if (j < 0 || j >= p_.ny)
+        continue;
+      const BndNode *r0 = p_.bnd + row0_[(size_t)y], *r1 = p_.bnd + row0_[(size_t)y + 1];
+      if (r0 == r1) continue;
+      // (on a periodic axis also the parts past either end; a plate narrower than
+      // that is one with some anywhere)
+      if (p_.px && x1 - x0 >= p_.nx) return true;
+      for (int sh = p_.px ? -1 : 0; sh <= (p_.px ? 1 : 0); sh++) {
+        const int a = x0 + sh * p_.nx, b = x1 + sh * p_.nx;
+        const BndNode *r = std::lower_bound(r0, r1, a, [](const BndNode &n, int v) { return n.i < v; });
+        if (r != r1 && r->i < b) return true;
+      }
+    }
+    return false;
   }
   int id(int i, int j) const { return (j - ly_) * gw_ + (i - lx_); }
   bool inside(int i, int j) const { return i >= lx_ && i < lx_ + gw_ && j >= ly_ && j < ly_ + gh_; }
@@ -404,11 +432,12 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
     bool ok = false;
   };
   std::vector<Job> jobs;
-  int64_t nodes = 0;
+  int64_t nodes = 0, bounded = 0;
   for (size_t p = 0; p < plates.size(); p++) {
     PatchCutter c(plates[p], K, rows, inner);
     for (const auto &b : c.bands()) jobs.push_back(Job{(int)p, b, {}, false});
     nodes += (int64_t)plates[p].nx * plates[p].ny;
+    bounded += plates[p].nb;
   }
   std::atomic<size_t> next{0};
   std::atomic<bool> failed{false};
@@ -429,9 +458,10 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
       failed = true;
     }
   };
-  // (a thread costs about as much as cutting a quarter of a million nodes)
+  // (a thread costs about as much as cutting a quarter of a million nodes or half a
+  // thousand boundary nodes)
   const size_t want = (size_t)std::min<int64_t>(
-      std::min<int64_t>(16, (int64_t)std::thread::hardware_concurrency()), nodes / (1 << 18));
+      std::min<int64_t>(16, (int64_t)std::thread::hardware_concurrency()), nodes / (1 << 18) + bounded / 512);
   std::vector<std::thread> pool;
   try {
     for (size_t i = 1; i < std::min(want, jobs.size()); i++) pool.emplace_back(work);
