@@ -105,9 +105,9 @@ typedef struct {
                                 LBM_READ_EQ_OLD (M2): the equilibrium of eq. LBE_mod is that
                                 of the boundary node's populations at t, not that of the
                                 time-averaged populations.  With either bit on any plate
-                                the context runs each step's boundary work in a launch of
-                                its own after the interior launch (no two-step pairs;
-                                slower, the same update) and lbm_autotune returns
+                                tile launches (lbm_set_tiling with steps = 1) run each
+                                step's boundary work in a launch of its own (no two-step
+                                pairs; slower, the same update) and lbm_autotune returns
                                 LBM_E_STATE.                                              */
 } lbm_plate;
 
@@ -207,11 +207,11 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
  * Newmark update, boundary reset, LBE with the second-row rule, and the
  * synchronization after every l-th step).  Stream-ordered and asynchronous:
  * returns once the work is enqueued.  Several steps are taken per launch in
- * patches held in registers (block passes) unless a plate uses readings other
- * than R1 + M1, a body is too dense in boundary nodes to be cut into patches,
- * or lbm_set_tiling asked for one step per launch; the tile launches of a
- * tiling (lbm_set_tiling) serve those cases, with the same results bit for
- * bit.  With two-step tile launches part of the work
+ * patches held in registers (block passes) unless a body is too dense in
+ * boundary nodes to be cut into patches, the call is a single step of plates
+ * too large for the Infinity Cache, or lbm_set_tiling asked for one step per
+ * launch; the tile launches of a tiling (lbm_set_tiling) serve those cases,
+ * with the same results bit for bit.  With two-step tile launches part of the work
  * runs on a second stream of the library's that forks from and joins back
  * into the context's stream with events within the call (see
  * lbm_use_overlap), so to the caller the work is ordered on the context's

@@ -28,6 +28,12 @@
 // wide ones such patches owned 4 to 11 rows each of 28 to 42; 1024^2 was cut
 // into 418 patches with boundary nodes, now 146, 256 plates 3564 per 16, now 1212).
 //
+// Plates of other readings (VAR) take the same patches: the flux of eq.
+// correction-f that streams into a boundary node comes from the march, the node's
+// thread keeps its stored populations and leaves one pulled population per
+// direction.  (With one interior and one boundary launch per step 257^2 FP64 took
+// 30 us per step, now 6.8.)
+//
 // k_inner takes the other patches of large plates with four waves and up to 256
 // registers per lane, so that two workgroups share a CU and one's loads and
 // stores run beside the other's steps (one workgroup of eight waves loaded and
@@ -78,10 +84,15 @@ __device__ __forceinline__ double from_east(double v) {
 }
 
 // Per field of a boundary node: the reset field and the population pulled
-// from it.
-template <class C>
+// from it (VAR: some plate uses readings other than R1 and M1; the flux of eq.
+// correction-f is then not 0 and each neighbour pulls another population).
+template <class C, bool VAR>
 struct BndOut {
   C fld[2], pull[2];
+};
+template <class C>
+struct BndOut<C, true> {
+  C fld[2], pull[2][4], j[2][2];
 };
 // State of a boundary node between steps: u, du/dt, and its boundary data.
 template <class U>
@@ -104,7 +115,7 @@ struct EdgeLds {
   typename CD::C edge[2][2][4][64 * W];
 };
 
-template <class CD, int M>
+template <class CD, int M, bool VAR>
 struct BlockLds : EdgeLds<CD, kWaves> {
   using C = typename CD::C;
   using U = typename CD::U;
@@ -114,7 +125,7 @@ struct BlockLds : EdgeLds<CD, kWaves> {
   PTask rec[kBlockTasks];
   BndState<U> st[kBlockTasks];
   U stress[kBlockGrads][3];
-  BndOut<C> out[kBlockTasks];
+  BndOut<C, VAR> out[kBlockTasks];
 };
 
 // One axis of a finite-difference stencil at patch node l, from its code:
@@ -148,14 +159,17 @@ struct AxisStencil {
 };
 
 // The gradient node of a thread (patches with boundary nodes) and, if that is
-// a boundary node, its rest and moving population of the previous step.
-template <class CD>
+// a boundary node, its rest and moving population of the previous step (VAR: its
+// stored populations).
+template <class CD, bool VAR>
 struct GradDuty {
   using C = typename CD::C;
   using U = typename CD::U;
+  using Slot = typename CD::Slot;
   int l = -1, task = -1;
   AxisStencil sx, sy;
   C fo[2][2];
+  Slot old[2][5];
 
   __device__ __forceinline__ void load(const DevState &s, const BlockArgs &a, const Patch &t,
                                        const PlateDev &P, int last) {
@@ -169,10 +183,9 @@ struct GradDuty {
     const int64_t k = s.bnd[a.tasks[t.b0 + task].bnd].node;
 #pragma unroll
     for (int fl = 0; fl < 2; fl++) {
-      typename CD::Slot r5[5];
       C f[5];
-      CD::load_raw(s, a.in, fl, k, r5);
-      CD::raw_to_pops(P, fl, r5, f);
+      CD::load_raw(s, a.in, fl, k, old[fl]);
+      CD::raw_to_pops(P, fl, old[fl], f);
       fo[fl][0] = f[0];
       fo[fl][1] = f[1];
     }
@@ -192,7 +205,11 @@ struct GradDuty {
 #pragma unroll
     for (int q = 0; q < 3; q++) lds.stress[threadIdx.x][q] = sg[q];
     if (!reset || task < 0) return;
-    BndOut<C> o;
+    if constexpr (VAR) {
+      reset_by_readings(P, lds, g);
+      return;
+    } else {
+    BndOut<C, VAR> o;
 #pragma unroll
     for (int fl = 0; fl < 2; fl++) {
       o.fld[fl] = fl == 0 ? (C)(g[0] + g[3]) : (C)(g[2] - g[1]);
@@ -207,20 +224,55 @@ struct GradDuty {
       fo[fl][1] = fn[1];
     }
     lds.out[task] = o;
+    }
+  }
+
+  // The same under the plate's readings (see pull_from_boundary in
+  // lbm_kernels.hip): R2 takes the flux the march has left in lds.out, R1 that of
+  // the previous populations; M2 collides with their equilibrium.
+  template <class L>
+  __device__ __forceinline__ void reset_by_readings(const PlateDev &P, L &lds, const U g[4]) {
+    BndOut<C, true> &o = lds.out[task];
+#pragma unroll
+    for (int fl = 0; fl < 2; fl++) {
+      const C fld = fl == 0 ? (C)(g[0] + g[3]) : (C)(g[2] - g[1]);
+      C jox, joy, fn[5], f[5], e[5];
+      CD::raw_flux(old[fl], jox, joy);
+      const bool streamed = P.readings & RD_FLUX_STREAMED;
+      const C jx = streamed ? o.j[fl][0] : jox, jy = streamed ? o.j[fl][1] : joy;
+      CD::eq_pops(P, fl, fld, jx, jy, fn);
+      CD::raw_to_pops(P, fl, old[fl], f);
+#pragma unroll
+      for (int q = 0; q < 5; q++) f[q] = C(0.5) * (fn[q] + f[q]);
+      if (P.readings & RD_EQ_OLD) {
+        CD::eq_pops(P, fl, CD::raw_rho(old[fl]), jox, joy, e);
+#pragma unroll
+        for (int q = 1; q < 5; q++) o.pull[fl][q - 1] = f[q] - C(2.0) * (f[q] - e[q]);
+      } else {
+        C r;
+        collide_pops<CD>(P, fl, f, r, e);
+#pragma unroll
+        for (int q = 1; q < 5; q++) o.pull[fl][q - 1] = e[q];
+      }
+      o.fld[fl] = fld;
+      o.j[fl][0] = jx;
+      o.j[fl][1] = jy;
+      CD::eq_raw(P, fl, fld, jx, jy, old[fl]);
+    }
   }
 };
 
 // The boundary accelerations of a patch, by its last wave; the barriers are
 // those of block_march<BND>.
-template <class CD, int M>
+template <class CD, int M, bool VAR>
 __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArgs &a, const Patch &t,
-                                               const PlateDev &P, BlockLds<CD, M> &lds) {
+                                               const PlateDev &P, BlockLds<CD, M, VAR> &lds) {
   using U = typename CD::U;
   constexpr int kLast = 64 * M * (kWaves - 1) - 1;
   const int lane = threadIdx.x & 63;
   const int nb = t.b1 - t.b0;
   const unsigned long long n0 = s.counter[a.in];
-  GradDuty<CD> duty;
+  GradDuty<CD, VAR> duty;
   duty.load(s, a, t, P, kLast);
   for (int i = lane; i < nb; i += 64) {
     const PTask T = a.tasks[t.b0 + i];
@@ -296,7 +348,7 @@ __device__ __forceinline__ void block_boundary(const DevState &s, const BlockArg
 
 // The interior waves of a patch; BND: it holds boundary nodes (the last wave
 // is block_boundary's).
-template <class CD, int M, int kW, bool BND, class Lds>
+template <class CD, int M, int kW, bool BND, bool VAR, class Lds>
 __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &a, const Patch &t,
                                             const PlateDev &P, Lds &lds) {
   using C = typename CD::C;
@@ -330,7 +382,7 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
     const int r = grp * M + m;
     return col >= t.ox0 && col < t.ox1 && r >= t.oy0 && r < t.oy1;
   };
-  GradDuty<CD> duty;
+  GradDuty<CD, VAR> duty;
   if constexpr (BND) duty.load(s, a, t, P, kLast);
   // task + 1 (0: none) of a boundary node (low half of up[0]) or of a second-row
   // node's upwind boundary nodes W, S, E, N; which (row, direction) any lane of
@@ -433,6 +485,26 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
       update(0, lo, rho[1]);
       update(M - 1, rho[M - 2], hi);
     }
+    if constexpr (BND && VAR) {
+      // flux of eq. correction-f under reading R2: what streams into a boundary
+      // node from its body neighbours
+      if (P.readings & RD_FLUX_STREAMED) {
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+          if (!(some_b >> m & 1u)) continue;
+#pragma unroll
+          for (int fl = 0; fl < 2; fl++) {
+            const C fw = from_west(fs[m][fl][1]), fe = from_east(fs[m][fl][3]);
+            const C fb = m > 0 ? fs[m > 0 ? m - 1 : 0][fl][2] : from_below(2 + fl);
+            const C fa = m + 1 < M ? fs[m + 1 < M ? m + 1 : m][fl][4] : from_above(2 + fl);
+            if (!(cl[m] & CL_B) || !up[m][0]) continue;
+            C *j2 = lds.out[up[m][0] - 1].j[fl];
+            j2[0] = (C(0) + (cl[m] & NB_W ? fw : C(0))) + (cl[m] & NB_E ? -fe : C(0));
+            j2[1] = (C(0) + (cl[m] & NB_S ? fb : C(0))) + (cl[m] & NB_N ? -fa : C(0));
+          }
+        }
+      }
+    }
     if constexpr (BND) {
       __syncthreads();
       duty.run(P, lds, true);
@@ -458,8 +530,15 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
           if (some >> (4 * m + al - 1) & 1u) {
             const uint32_t w2 = up[m][(al - 1) >> 1];
             const uint32_t ti = cl[m] & CL_S ? ((al - 1) & 1 ? w2 >> 16 : w2 & 0xffffu) : 0u;
-            const BndOut<C> &o = lds.out[ti ? ti - 1 : 0];
-            const C p0 = o.pull[0], p1 = o.pull[1];
+            const auto &o = lds.out[ti ? ti - 1 : 0];
+            C p0, p1;
+            if constexpr (VAR) {
+              p0 = o.pull[0][al - 1];
+              p1 = o.pull[1][al - 1];
+            } else {
+              p0 = o.pull[0];
+              p1 = o.pull[1];
+            }
             f[0][al] = ti ? p0 : f[0][al];
             f[1][al] = ti ? p1 : f[1][al];
           }
@@ -469,11 +548,14 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
       if constexpr (BND) {
         if (some_b >> m & 1u) {
           const bool isb = (cl[m] & CL_B) && up[m][0];
-          const BndOut<C> &o = lds.out[isb ? up[m][0] - 1 : 0];
+          const auto &o = lds.out[isb ? up[m][0] - 1 : 0];
 #pragma unroll
           for (int fl = 0; fl < 2; fl++) {
             Slot q5[5];
-            CD::eq_raw(P, fl, o.fld[fl], q5);
+            if constexpr (VAR)
+              CD::eq_raw(P, fl, o.fld[fl], o.j[fl][0], o.j[fl][1], q5);
+            else
+              CD::eq_raw(P, fl, o.fld[fl], q5);
 #pragma unroll
             for (int q = 0; q < 5; q++) raw[m][fl][q] = isb ? q5[q] : raw[m][fl][q];
           }
@@ -499,10 +581,10 @@ __device__ __forceinline__ void block_march(const DevState &s, const BlockArgs &
   }
 }
 
-template <int ST, int M>
+template <int ST, int M, bool VAR = false>
 __global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArgs a) {
   using CD = typename CodecOf<ST>::type;
-  __shared__ BlockLds<CD, M> lds;
+  __shared__ BlockLds<CD, M, VAR> lds;
   if (a.count && blockIdx.x == 0 && threadIdx.x == 0)
     s.counter[a.out] = s.counter[a.in] + (unsigned long long)a.steps;
   const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);  // (scalar branches)
@@ -511,11 +593,11 @@ __global__ void __launch_bounds__(kBlockThreads, 2) k_block(DevState s, BlockArg
   const Patch t = a.patches[ix];
   const PlateDev P = s.plates[t.plate];
   if (t.b1 <= t.b0)
-    block_march<CD, M, kWaves, false>(s, a, t, P, lds);
+    block_march<CD, M, kWaves, false, VAR>(s, a, t, P, lds);
   else if (wv < kWaves - 1)
-    block_march<CD, M, kWaves - 1, true>(s, a, t, P, lds);
+    block_march<CD, M, kWaves - 1, true, VAR>(s, a, t, P, lds);
   else
-    block_boundary<CD, M>(s, a, t, P, lds);
+    block_boundary<CD, M, VAR>(s, a, t, P, lds);
 }
 
 // (two waves per SIMD: two workgroups of four waves, or one of eight, per CU)
@@ -529,12 +611,17 @@ __global__ void __launch_bounds__(64 * W, 2) k_inner(DevState s, BlockArgs a) {
   if (ix >= a.n) return;
   const Patch t = a.patches[ix];
   const PlateDev P = s.plates[t.plate];
-  block_march<CD, M, W, false>(s, a, t, P, lds);
+  block_march<CD, M, W, false, false>(s, a, t, P, lds);
 }
 
 template <int ST>
-hipError_t launch_block_t(const DevState &s, const BlockArgs &a, int rows, hipStream_t st) {
+hipError_t launch_block_t(const DevState &s, const BlockArgs &a, int rows, bool var, hipStream_t st) {
   const dim3 grid(8 * a.q), th(kBlockThreads);
+  if (var) {
+    if (rows != 3) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_block<ST, 3, true>), grid, th, 0, st, s, a);
+    return hipGetLastError();
+  }
   if (rows == 3) {
     hipLaunchKernelGGL((k_block<ST, 3>), grid, th, 0, st, s, a);
     return hipGetLastError();
@@ -577,11 +664,11 @@ hipError_t launch_block(int storage, const DevState &s, const BlockWork &w, int 
   if (w.n_patches < 1 || steps < 1) return hipErrorInvalidValue;
   const BlockArgs a{w.patches, w.tasks, w.grads, w.n_patches, (w.n_patches + 7) / 8, in, out, steps, 1};
   switch (storage) {
-    case LBM_STORE_F64: return launch_block_t<LBM_STORE_F64>(s, a, w.rows, st);
-    case LBM_STORE_F32: return launch_block_t<LBM_STORE_F32>(s, a, w.rows, st);
-    case LBM_STORE_F32DEV: return launch_block_t<LBM_STORE_F32DEV>(s, a, w.rows, st);
-    case LBM_STORE_F16DEV: return launch_block_t<LBM_STORE_F16DEV>(s, a, w.rows, st);
-    case LBM_STORE_BF16DEV: return launch_block_t<LBM_STORE_BF16DEV>(s, a, w.rows, st);
+    case LBM_STORE_F64: return launch_block_t<LBM_STORE_F64>(s, a, w.rows, w.var, st);
+    case LBM_STORE_F32: return launch_block_t<LBM_STORE_F32>(s, a, w.rows, w.var, st);
+    case LBM_STORE_F32DEV: return launch_block_t<LBM_STORE_F32DEV>(s, a, w.rows, w.var, st);
+    case LBM_STORE_F16DEV: return launch_block_t<LBM_STORE_F16DEV>(s, a, w.rows, w.var, st);
+    case LBM_STORE_BF16DEV: return launch_block_t<LBM_STORE_BF16DEV>(s, a, w.rows, w.var, st);
   }
   return hipErrorInvalidValue;
 }

@@ -165,6 +165,10 @@ struct PopCodec {
   __device__ static void eq_raw(const PlateDev &P, int fl, C rho, Slot r[5]) {
     eq_pops(P, fl, rho, C(0), C(0), r);
   }
+  // the same with flux J
+  __device__ static void eq_raw(const PlateDev &P, int fl, C rho, C jx, C jy, Slot r[5]) {
+    eq_pops(P, fl, rho, jx, jy, r);
+  }
   __device__ static void store_raw(const DevState &s, int b, int fl, int64_t k, const Slot r[5]) {
 #pragma unroll
     for (int q = 0; q < 5; q++) stg<T>(s.pop[b][fl][q], k, r[q]);
@@ -356,6 +360,12 @@ struct DevCodec {
   __device__ static void eq_raw(const PlateDev &, int, C rho, Slot r[5]) {
     r[0] = __float_as_uint(rho);
     r[1] = r[2] = r[3] = r[4] = 0u;
+  }
+  __device__ static void eq_raw(const PlateDev &, int, C rho, C jx, C jy, Slot r[5]) {
+    r[0] = __float_as_uint(rho);
+    r[1] = __float_as_uint(jx);
+    r[2] = __float_as_uint(jy);
+    r[3] = r[4] = 0u;
   }
   __device__ static void store_raw(const DevState &s, int b, int fl, int64_t k, const Slot r[5]) {
 #pragma unroll

@@ -96,9 +96,10 @@ struct lbm_ctx {
   int64_t n_two = 0;  // body nodes in two-step tiles
   int64_t n_body = 0;
   int sync_every = 0;
-  // some plate uses readings other than R1 + M1: every step's boundary work
-  // runs in the boundary kernel (the interior kernel's prologues carry only
-  // the default readings), so every step is a segment of its own
+  // some plate uses readings other than R1 + M1: without block passes every
+  // step's boundary work runs in the boundary kernel (the interior kernel's
+  // prologues carry only the default readings), so every step is then a segment
+  // of its own
   bool variant_readings = false;
 
   std::vector<BndNode> bnd;
@@ -1273,7 +1274,7 @@ bool overlapped_pair(const lbm_ctx *c, int64_t n) {
 // One block pass of q steps from buffer `in` to the other one.
 hipError_t enqueue_block(lbm_ctx *c, int in, int q, hipStream_t st) {
   const BlockWork w{c->d_patches, c->d_inner, c->d_ptasks, c->d_pgrads, (int)c->plan.patches.size(),
-                    (int)c->plan.inner.size(), c->plan.rows, c->plan.inner_rows};
+                    (int)c->plan.inner.size(), c->plan.rows, c->plan.inner_rows, c->variant_readings};
   hipError_t e = hipSuccess;
   if (w.n_patches > 0) e = launch_block(c->storage, c->ds, w, in, in ^ 1, q, st);
   if (e == hipSuccess && w.n_inner > 0) e = launch_inner(c->storage, c->ds, w, in, in ^ 1, q, st);
@@ -1404,9 +1405,9 @@ hipError_t enqueue_segment(lbm_ctx *c, int64_t s, int64_t k, int &cur, int &prev
 }
 
 // Length of the segment starting at step s (ends at the next synchronization;
-// one step with readings other than R1 + M1).
+// one step of the tile launches with readings other than R1 + M1).
 int64_t segment_limit(const lbm_ctx *c, int64_t s, int64_t n) {
-  if (c->variant_readings) return std::min<int64_t>(n, 1);
+  if (c->variant_readings && !c->block) return std::min<int64_t>(n, 1);
   if (c->sync_every <= 0) return n;
   return std::min<int64_t>(n, c->sync_every - s % c->sync_every);
 }
@@ -1686,7 +1687,9 @@ bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &
   const bool f64 = c->storage == LBM_STORE_F64, bounded = !c->bnd.empty();
   const int R = block_inner_rows(c->storage);
   std::vector<BlockShape> small;
-  if (!bounded)
+  if (c->variant_readings && bounded)
+    small = {};
+  else if (!bounded)
     small = {{6, 3, kInnerSmall}, {5, 3, kInnerSmall}, {4, 3, kInnerSmall}};
   else if (f64)
     small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}};
@@ -1721,6 +1724,13 @@ bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &
     if (bounded) fill(plan.inner.size());
     return true;
   }
+  if (c->variant_readings && bounded) {
+    // (the flux and four populations pulled per boundary node leave LDS for three
+    // rows per wave in FP64)
+    if (!make_patch_plan(v, 5, 3, 24, plan) && !make_patch_plan(v, 4, 3, 24, plan)) return false;
+    fill(plan.inner.size());
+    return true;
+  }
   const BlockShape large = f64 ? BlockShape{5, 4, R} : c->storage == LBM_STORE_F32 ? BlockShape{6, 6, R}
                            : c->storage == LBM_STORE_F32DEV ? BlockShape{6, 5, R} : BlockShape{5, 5, R};
   // (a plate too dense with boundary nodes for K steps may still do four)
@@ -1744,6 +1754,7 @@ bool plan_blocks(lbm_ctx *c) {
     v[p].ny = h.ny;
     v[p].px = h.px;
     v[p].py = h.py;
+    v[p].streamed = (c->pd[p].readings & RD_FLUX_STREAMED) != 0;
     v[p].cls = h.cls.data();
     v[p].bnd = c->bnd.data() + h.b0;
     v[p].b0 = h.b0;
@@ -2130,7 +2141,7 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   c->rows = 8;
   c->edge_rows = 2;
   c->align = c->n_body < ((int64_t)4 << 20) ? 0 : 16;
-  if (!c->variant_readings) c->block = c->can_block = plan_blocks(c);
+  c->block = c->can_block = plan_blocks(c);
   if (new_tiles(c) != LBM_OK) return bail(LBM_E_NOMEM, c->err);
   if (hipEventCreateWithFlags(&c->flag_ev, hipEventDisableTiming) != hipSuccess)
     return bail(LBM_E_DEVICE, "event creation failed");

@@ -34,6 +34,7 @@ struct BlockWork {
   const PTask *tasks;
   const PGrad *grads;
   int n_patches, n_inner, rows, inner_rows;
+  bool var;  // some plate uses readings other than R1 and M1 (rows: 3)
 };
 hipError_t launch_block(int storage, const DevState &s, const BlockWork &w, int in, int out, int steps,
                         hipStream_t stream) __attribute__((weak));

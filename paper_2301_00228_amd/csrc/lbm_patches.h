@@ -19,6 +19,7 @@ struct PatchPlate {
   int index = 0;                 // plate
   int nx = 0, ny = 0;
   bool px = false, py = false;   // periodic axes
+  bool streamed = false;         // reading R2
   const uint8_t *cls = nullptr;  // dense nx * ny class bytes
   const BndNode *bnd = nullptr;  // the plate's boundary records, row-major
   int64_t nb = 0, b0 = 0;        // their number, index of the first one
@@ -121,7 +122,8 @@ class PatchCutter {
   // Rules, from the method.  Populations of t + j (F) need at an interior
   // node those of t + j - 1 at the node and its four neighbours, and at a
   // neighbour that is a boundary node also its reset field at t + j; at a
-  // boundary node u of t + j on its finite-difference stencil.  u, du/dt of
+  // boundary node u of t + j on its finite-difference stencil (and, under reading
+  // R2, the neighbours' F of t + j - 1).  u, du/dt of
   // t + j (U) need those of t + j - 1 at the node and, at an interior node,
   // the neighbours' fields of t + j - 1, at a boundary node u of t + j - 1 on
   // the stencils of the node and its body neighbours.
@@ -302,6 +304,7 @@ class PatchCutter {
     if (l == 0) return;
     if (c_[(size_t)k] & CL_B) {
       need_stencil(i, j, l);
+      if (p_.streamed) neighbours(i, j, [&](int a, int b) { need_f(a, b, l - 1); });
       return;
     }
     need_f(i, j, l - 1);

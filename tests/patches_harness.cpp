@@ -5,7 +5,7 @@
 //
 // stdin: n_plates, then per plate: nx ny periodic_x periodic_y, ny rows of
 //        nx 0/1; n_plans, then per plan: steps, rows per wave, rows
-//        of a patch without boundary nodes
+//        of a patch without boundary nodes, 1 for reading R2
 // stdout: per plan "patches P bounded B tasks T violations V"
 #include <cstdio>
 #include <iostream>
@@ -70,8 +70,9 @@ int main() {
   int nplans, total = 0;
   std::cin >> nplans;
   for (int q = 0; q < nplans; q++) {
-    int K, rows, inner, bad = 0, bounded = 0;
-    std::cin >> K >> rows >> inner;
+    int K, rows, inner, streamed, bad = 0, bounded = 0;
+    std::cin >> K >> rows >> inner >> streamed;
+    for (auto &p : pp) p.streamed = streamed != 0;
     PatchPlan plan;
     if (!make_patch_plan(pp, K, rows, inner, plan)) {
       printf("plan %d %d %d: not cut\n", K, rows, inner);
@@ -201,6 +202,8 @@ int main() {
               bool ok = (c & CL_IN) != 0;
               if (ok && (c & CL_B)) {
                 ok = stencil(U1, a, b);
+                for (int d = 0; d < 4; d++)
+                  if (streamed && (c & nbit[d])) ok = ok && get(F, a + di[d], b + dj[d]);
               } else if (ok) {
                 ok = get(F, a, b);
                 for (int d = 0; d < 4; d++) {

@@ -85,6 +85,19 @@ def test_every_shape_of_patches_bitwise(storage):
         same([c], storage, (7, 52))
 
 
+@pytest.mark.parametrize("readings", [(1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("storage", STORAGES)
+def test_other_readings_bitwise(storage, readings):
+    hole = I.plate_with_hole(n=150, radius=23, sigma=4.0, steps=0, a0_phi=0.99)
+    shear = E.paper_case("shear", 70, 50, t_end=1.0)
+    open_x = clamped(90, 61, a0_phi=0.99)
+    open_x.periodic, open_x.bcs = (True, False), []
+    for c in (hole, shear, open_x):
+        c.readings = readings
+    # (with a plate of the default readings, which then runs in the same launch)
+    same([hole, shear, open_x, clamped(40, 37, a0_phi=0.99)], storage, (6, 47, 31))
+
+
 def test_strip_with_holes_matches_the_oracle():
     case = I.strip_with_holes(nx=500, ny=120, sigma=6.0, pulses=3, steps=103, seed_index=7)
     ref, _ = run_case(case)

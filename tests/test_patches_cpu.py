@@ -24,9 +24,9 @@ SOURCES = [os.path.join(ROOT, "tests", "patches_harness.cpp"),
            os.path.join(ROOT, "tests", "tiles_harness.cpp"),
            os.path.join(ROOT, "include", "lbm.h")]
 SOURCES += [os.path.join(CSRC, f) for f in ("lbm_host.cpp", "lbm_types.h", "lbm_kernels.h", "lbm_patches.h")]
-# steps, rows per wave, rows of a patch without boundary nodes
-PLANS = [(4, 4, 32), (2, 2, 16), (1, 2, 8), (3, 4, 28), (5, 3, 24), (5, 4, 28), (5, 5, 40), (6, 3, 16), (6, 5, 40),
-         (6, 6, 48)]
+# steps, rows per wave, rows of a patch without boundary nodes, reading R2
+PLANS = [(4, 4, 32, 0), (2, 2, 16, 0), (1, 2, 8, 0), (3, 4, 28, 0), (5, 3, 24, 0), (5, 4, 28, 0), (5, 5, 40, 0),
+         (6, 3, 16, 0), (6, 5, 40, 0), (6, 6, 48, 0), (5, 3, 24, 1), (4, 3, 24, 1)]
 
 
 @pytest.fixture(scope="module")
@@ -94,4 +94,4 @@ def test_bodies_that_are_mostly_boundary(harness):
         b[o:o + 2, :] = 1
     for o in range(0, 48, 8):
         b[:, o:o + 2] = 1
-    check(harness, [(a, (False, False)), (b, (False, False))], [(2, 2, 16), (1, 2, 8), (2, 4, 32)])
+    check(harness, [(a, (False, False)), (b, (False, False))], [(2, 2, 16, 0), (1, 2, 8, 0), (2, 4, 32, 0)])
