@@ -1676,10 +1676,12 @@ struct BlockShape {
 // 0.85 with them: 256^2 clamped FP64, us per pass: m = 3, K = 3, 4, 5 16.9, 19.6,
 // 21.9; m = 4, K = 4, 5, 6 26.0, 28.9, 33.0), once per round of patches over the
 // CUs: the shape with the least of that per step is taken, all patches in one
-// launch.  Past two rounds throughput counts instead: patches without boundary
-// nodes go to k_inner, two to a CU, and are as large as that leaves registers
-// for.  Us per step, one launch / two: 640^2 FP32 6.3 / 9.0, 1031 x 517 FP32
-// 8.2 / 9.5, FP64 13.7 / 14.0, 1024^2 FP32 13.9 / 12.0, FP64 21.9 / 18.4.
+// launch.  Past one round in FP64, two in the 4-byte storages, throughput counts
+// instead: patches without boundary nodes go to k_inner, two to a CU, and are as
+// large as that leaves registers for.  Us per step, one launch / two: within a
+// round 640^2 FP32 6.3 / 9.0; at two 1031 x 517 FP32 8.7 / 9.2, F16DEV 11.1 / 11.6,
+// F32DEV 9.7 / 9.1, FP64 13.3 / 11.9, 640^2 FP64 11.4 / 10.4; beyond 1024^2 FP32
+// 13.9 / 11.3, FP64 21.9 / 17.1.
 // K is there where the halo's growth meets the passes saved: 4096^2 with
 // a hole, K = 4, 5, 6: FP64 258, 209, 217; FP32 141, 116, 107; F32DEV 170, 138,
 // 129; F16DEV 157, 132, 149.
@@ -1694,13 +1696,13 @@ bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &
   else if (f64)
     small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}};
   else
-    small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}, {6, 5, 40}, {6, 6, 48}};
+    small = {{5, 3, 24}, {5, 4, 32}, {4, 4, 32}, {6, 5, 40}, {5, 5, 40}, {6, 6, 48}, {5, 6, 48}};
   auto cost = [&](const BlockShape &b, int64_t patches) {
     const int m = bounded ? b.rows : b.inner / (kBlockThreads / 64);
     return (double)((patches + kCus - 1) / kCus) * (12 + b.K * m) / b.K;
   };
   double best = 0;
-  const int64_t most = bounded ? 2 * kCus : kCus;
+  const int64_t most = bounded && !f64 ? 2 * kCus : kCus;
   for (const BlockShape &b : small) {
     // (at least as many as the body's nodes fill)
     const int64_t own = (int64_t)(kBlockCols - 2 * b.K) * (b.inner - 2 * b.K);
