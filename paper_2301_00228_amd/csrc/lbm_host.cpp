@@ -177,7 +177,8 @@ struct lbm_ctx {
   // asks for several steps per pass; not under one with steps = 1.
   PatchPlan plan;
   bool can_block = false;
-  bool tables = false;  // the tiles' prologue lists are in place (see ensure_tables)
+  bool tiles_up = false;  // the device's tile lists are those of the tiling (see ready)
+  bool tables = false;    // the tiles' prologue lists are in place (see ensure_tables)
   bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
   Patch *d_patches = nullptr, *d_inner = nullptr;
   PTask *d_ptasks = nullptr;
@@ -1100,6 +1101,7 @@ lbm_status upload_tile_list(lbm_ctx *c, const std::vector<Tile> &v, Tile *&d, si
 }
 
 lbm_status upload_tiles(lbm_ctx *c) {
+  c->tiles_up = false;
   c->etiles.clear();
   c->ftiles.clear();
   c->dtiles.clear();
@@ -1119,7 +1121,9 @@ lbm_status upload_tiles(lbm_ctx *c) {
   if (st) return st;
   st = upload_tile_list(c, c->dtiles, c->d_dtiles, c->dtiles_cap);
   if (st) return st;
-  return upload_tile_list(c, c->etiles, c->d_etiles, c->etiles_cap);
+  st = upload_tile_list(c, c->etiles, c->d_etiles, c->etiles_cap);
+  c->tiles_up = st == LBM_OK;
+  return st;
 }
 
 // The state is past the Infinity Cache (a pass over it moves more than that).
@@ -1142,9 +1146,11 @@ lbm_status ensure_tables(lbm_ctx *c) {
   return LBM_OK;
 }
 
-// The tiles after a change of the tiling.
+// The tiles after a change of the tiling.  (Captured graphs hold the lists'
+// addresses; a failure leaves the lists to `ready`.)
 lbm_status new_tiles(lbm_ctx *c) {
-  c->tables = false;
+  drop_graph(c);
+  c->tables = c->tiles_up = false;
   build_tiles(c);
   return c->block && !past_cache(c) ? upload_tiles(c) : ensure_tables(c);
 }
@@ -1182,26 +1188,39 @@ lbm_status ensure_third(lbm_ctx *c) {
   HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
   const int64_t N = c->n_alloc;
   const int nsl = slot_count(c->storage);
+  // (all of the buffer or none of it: what a failure leaves behind is freed)
+  struct Parts {
+    lbm_ctx *c;
+    void *pop[2][5] = {}, *uv[4] = {};
+    ~Parts() {
+      for (auto &f : pop)
+        for (void *p : f) dev_free(c, p);
+      for (void *p : uv) dev_free(c, p);
+    }
+  } part{c};
   for (int fl = 0; fl < 2; fl++)
     for (int sl = 0; sl < nsl; sl++) {
-      void *p = dev_alloc(c, (size_t)N * slot_bytes(c->storage));
+      void *&p = part.pop[fl][sl];
+      p = dev_alloc(c, (size_t)N * slot_bytes(c->storage));
       if (!p) return fail(c, LBM_E_NOMEM, "population allocation failed");
       HIP_TRY(c, hipMemset(p, 0, (size_t)N * slot_bytes(c->storage)), "memset");
-      c->ds.pop[2][fl][sl] = p;
     }
-  void *uv[4];
-  for (int q = 0; q < 4; q++) {
-    uv[q] = dev_alloc(c, (size_t)N * uv_bytes(c->storage));
-    if (!uv[q]) return fail(c, LBM_E_NOMEM, "u/v allocation failed");
+  for (void *&p : part.uv) {
+    p = dev_alloc(c, (size_t)N * uv_bytes(c->storage));
+    if (!p) return fail(c, LBM_E_NOMEM, "u/v allocation failed");
   }
   const int src = c->cur ^ 1;
   for (int comp = 0; comp < 2; comp++) {
-    HIP_TRY(c, hipMemcpy(uv[comp], c->ds.u[src][comp], (size_t)N * uv_bytes(c->storage),
+    HIP_TRY(c, hipMemcpy(part.uv[comp], c->ds.u[src][comp], (size_t)N * uv_bytes(c->storage),
                          hipMemcpyDeviceToDevice), "u copy");
-    HIP_TRY(c, hipMemcpy(uv[2 + comp], c->ds.v[src][comp], (size_t)N * uv_bytes(c->storage),
+    HIP_TRY(c, hipMemcpy(part.uv[2 + comp], c->ds.v[src][comp], (size_t)N * uv_bytes(c->storage),
                          hipMemcpyDeviceToDevice), "v copy");
-    c->ds.u[2][comp] = uv[comp];
-    c->ds.v[2][comp] = uv[2 + comp];
+  }
+  for (int fl = 0; fl < 2; fl++)
+    for (int sl = 0; sl < nsl; sl++) std::swap(c->ds.pop[2][fl][sl], part.pop[fl][sl]);
+  for (int comp = 0; comp < 2; comp++) {
+    std::swap(c->ds.u[2][comp], part.uv[comp]);
+    std::swap(c->ds.v[2][comp], part.uv[2 + comp]);
   }
   drop_graph(c);
   return LBM_OK;
@@ -1635,13 +1654,27 @@ lbm_status ensure_ahead(lbm_ctx *c) {
   return LBM_OK;
 }
 
+// What the launches of the path in use read and write is in place (also after a
+// call that could not finish: for want of memory, say, it leaves the lists of
+// another tiling, or none): the tile lists, and for the tile launches their
+// prologue lists and the buffer that two-step pairs go through.
+lbm_status ready(lbm_ctx *c) {
+  if (!c->tiles_up) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+    lbm_status st = new_tiles(c);
+    if (st) return st;
+  }
+  if (c->block) return LBM_OK;
+  lbm_status st = ensure_tables(c);
+  return st || !c->two ? st : ensure_third(c);
+}
+
 // What has to be in place before steps are enqueued from the current state;
 // a block pass leaves no boundary accelerations for the next step.
 lbm_status before_steps(lbm_ctx *c) {
-  if (!c->block) {
-    lbm_status st = ensure_tables(c);
-    return st ? st : ensure_ahead(c);
-  }
+  lbm_status st = ready(c);
+  if (st) return st;
+  if (!c->block) return ensure_ahead(c);
   c->ahead = false;
   return LBM_OK;
 }
@@ -1654,10 +1687,17 @@ lbm_status before_steps(lbm_ctx *c) {
 struct TilesFor {
   lbm_ctx *c;
   bool block;
-  TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block) {
-    if (n == 1 && past_cache(c)) c->block = false;
+  int two;
+  TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block), two(ctx->two) {
+    if (block && n == 1 && past_cache(c)) {
+      c->block = false;
+      c->two = 0;  // (no pairs)
+    }
   }
-  ~TilesFor() { c->block = block; }
+  ~TilesFor() {
+    c->block = block;
+    c->two = two;
+  }
 };
 
 // CUs of the GPU: workgroups of k_block that run at once.
@@ -2258,10 +2298,8 @@ lbm_status lbm_prepare_steps(lbm_ctx *c, int64_t n) {
   st = start(c);
   if (st) return st;
   const TilesFor tiles(c, n);
-  if (!c->block) {
-    st = ensure_tables(c);
-    if (st) return st;
-  }
+  st = ready(c);
+  if (st) return st;
   int64_t s = c->step;
   int cur = c->cur, prev = c->prev;
   while (n > 0) {
@@ -2413,6 +2451,8 @@ lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
                 "lanes must be 64, 128 or 256, rows >= 1, order 0..3, edge_rows >= 0, "
                 "align 0..4096, steps 0..2, edge_cols 0..lanes-4, stream_stores 0..1");
   HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  drop_graph(c);
+  c->tables = c->tiles_up = false;
   c->lanes = lanes;
   c->rows = rows;
   c->order = order;
@@ -2430,10 +2470,7 @@ lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
       return st3;
     }
   }
-  lbm_status st = new_tiles(c);
-  if (st) return st;
-  drop_graph(c);
-  return LBM_OK;
+  return new_tiles(c);
 }
 
 lbm_status lbm_use_graphs(lbm_ctx *c, int32_t enable) {
@@ -2448,10 +2485,7 @@ lbm_status lbm_use_overlap(lbm_ctx *c, int32_t enable) {
   HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
   c->overlap = enable != 0;
   // (the frame tiles are cut shorter with overlapped pairs)
-  lbm_status st = new_tiles(c);
-  if (st) return st;
-  drop_graph(c);
-  return LBM_OK;
+  return new_tiles(c);
 }
 
 lbm_status lbm_profile(lbm_ctx *c, int64_t n, double *ms, int64_t *launches) {
@@ -2467,10 +2501,6 @@ lbm_status lbm_profile(lbm_ctx *c, int64_t n, double *ms, int64_t *launches) {
     ~Restore() { c->block = block; }
   } restore{c, c->block};
   if (c->tiled) c->block = false;
-  if (!c->block && c->two) {
-    st = ensure_third(c);
-    if (st) return st;
-  }
   st = before_steps(c);
   if (st) return st;
   // Launches on one stream go back to back; the time between the events
@@ -2530,9 +2560,45 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   // a synchronization (nor n = 0): otherwise one real step is taken first.
   const bool syncs_now = c->sync_every > 0 && c->step % c->sync_every == 0;
   const bool fresh = !c->ahead;  // (a block pass leaves no populations of t_{n-1} either)
+  // Until the choice at the end: a call that ends before it leaves the tiling it
+  // found, whose lists `ready` puts back.
+  struct Keep {
+    lbm_ctx *c;
+    int lanes, rows, order, edge_rows, edge_cols, align, nt, two;
+    bool overlap, block;
+    void *scratch = nullptr;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    bool chosen = false;
+    explicit Keep(lbm_ctx *x)
+        : c(x), lanes(x->lanes), rows(x->rows), order(x->order), edge_rows(x->edge_rows),
+          edge_cols(x->edge_cols), align(x->align), nt(x->nt), two(x->two), overlap(x->overlap),
+          block(x->block) {}
+    ~Keep() {
+      if (scratch) (void)hipStreamSynchronize(c->stream);
+      dev_free(c, scratch);
+      if (e0) (void)hipEventDestroy(e0);
+      if (e1) (void)hipEventDestroy(e1);
+      if (chosen) return;
+      c->lanes = lanes;
+      c->rows = rows;
+      c->order = order;
+      c->edge_rows = edge_rows;
+      c->edge_cols = edge_cols;
+      c->align = align;
+      c->nt = nt;
+      c->two = two;
+      c->overlap = overlap;
+      c->block = block;
+      c->tables = c->tiles_up = c->ahead = false;
+      drop_graph(c);
+    }
+  } keep(c);
+  const bool had_third = have_third(c);
+  if (c->block && !had_third) c->two = 0;  // (the step below is no pair)
   c->block = false;
   st = before_steps(c);
   if (st) return st;
+  drop_graph(c);  // (they hold the addresses of the lists that the candidates replace)
   if (fresh || c->step == 0 || (syncs_now && c->sync_every > 1) || c->prev == 2) {
     HIP_TRY(c, enqueue_segment(c, c->step, 1, c->cur, c->prev, c->stream, nullptr),
             "step launch");
@@ -2544,18 +2610,17 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   const int64_t n = c->step;
   const size_t side_bytes = (size_t)std::max<int64_t>(1, c->ds.nsec) * 10 *
                             (c->storage == LBM_STORE_F64 ? sizeof(double) : sizeof(float));
-  void *side_scratch = dev_alloc(c, side_bytes);
+  void *const side_scratch = keep.scratch = dev_alloc(c, side_bytes);
   if (!side_scratch) return fail(c, LBM_E_NOMEM, "autotuner scratch allocation failed");
   // two-step candidates only if the third state buffer fits in memory
-  const bool had_third = have_third(c);
   const int max_steps = ensure_third(c) == LBM_OK ? 2 : 1;
   // state of the timed second launches: all buffers as allocated by now,
   // side buffer n & 1 replaced by the scratch buffer
   DevState ds_b = c->ds;
   ds_b.side[n & 1] = side_scratch;
-  hipEvent_t e0, e1;
-  HIP_TRY(c, hipEventCreate(&e0), "event");
-  HIP_TRY(c, hipEventCreate(&e1), "event");
+  HIP_TRY(c, hipEventCreate(&keep.e0), "event");
+  HIP_TRY(c, hipEventCreate(&keep.e1), "event");
+  const hipEvent_t e0 = keep.e0, e1 = keep.e1;
   int reps = steps;  // timed repetitions per candidate
   // Time body(st, k), which enqueues k repetitions of the timed launches on
   // stream st: eagerly (`reps` repetitions to warm up, then `reps` timed on the
@@ -2667,7 +2732,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
     }, graph);
   };
   double best = 1e300;
-  lbm_tiling bt{c->lanes, c->rows, c->order, c->edge_rows, c->align, c->two ? 2 : 1, c->edge_cols,
+  lbm_tiling bt{c->lanes, c->rows, c->order, c->edge_rows, c->align, keep.two ? 2 : 1, c->edge_cols,
                 c->nt};
   const bool ov_user = c->overlap;  // the search runs on one stream; the end may turn it on
   bool best_ov = false;
@@ -2869,9 +2934,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
                              (int)(n & 1), 0, c->stream),
           "boundary accelerations");
   (void)hipStreamSynchronize(c->stream);
-  dev_free(c, side_scratch);
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
+  keep.chosen = true;
   c->lanes = bt.lanes;
   c->rows = bt.rows;
   c->order = bt.order;
@@ -2886,7 +2949,6 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   if ((!c->two || c->block) && !had_third) release_third(c);
   st = new_tiles(c);
   if (st) return st;
-  drop_graph(c);
   if (best_ms) *best_ms = best;
   return LBM_OK;
 }
