@@ -209,8 +209,8 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
  * returns once the work is enqueued.  Several steps are taken per launch in
  * patches held in registers (block passes) unless a body is too dense in
  * boundary nodes to be cut into patches, the call is a single step of plates
- * too large for the Infinity Cache, or lbm_set_tiling asked for one step per
- * launch; the tile launches of a tiling (lbm_set_tiling) serve those cases,
+ * too large for the Infinity Cache, lbm_set_tiling asked for one step per
+ * launch, or lbm_use_blocks turned them off; the tile launches of a tiling (lbm_set_tiling) serve those cases,
  * with the same results bit for bit.  With two-step tile launches part of the work
  * runs on a second stream of the library's that forks from and joins back
  * into the context's stream with events within the call (see
@@ -308,8 +308,8 @@ lbm_status lbm_info(const lbm_ctx *ctx, lbm_info_t *info);
  *             whole cache lines);
  *  steps      1 (or 0): one time step per launch; 2: several steps per pass --
  *             block passes where the bodies allow them (see lbm_step), which
- *             do not depend on the other values, else tile launches in which
- *             tiles with no boundary
+ *             do not depend on the other values, else, or with lbm_use_blocks
+ *             off, tile launches in which tiles with no boundary
  *             or second-row node within two nodes of their area take two
  *             time steps per pass over HBM (the other tiles take the two
  *             steps in two launches); a tile then owns at most lanes-4
@@ -409,6 +409,16 @@ lbm_status lbm_use_graphs(lbm_ctx *ctx, int32_t enable);
  * captured step graphs.  Errors: LBM_E_INVAL (NULL ctx), LBM_E_NOMEM,
  * LBM_E_DEVICE. */
 lbm_status lbm_use_overlap(lbm_ctx *ctx, int32_t enable);
+
+/* Block passes (see lbm_step) where the bodies and the tiling allow them
+ * (nonzero, the default), or the tile launches of the tiling in every call (0):
+ * one step per launch under the default tiling and under steps = 1, two-step
+ * pairs under steps = 2.  The results are bitwise the same.  While off,
+ * lbm_autotune times and picks tilings only.  Synchronizes the stream;
+ * invalidates captured step graphs; may be changed between steps.  Errors:
+ * LBM_E_INVAL (NULL ctx), LBM_E_NOMEM (the buffer of two-step pairs; the
+ * setting holds, the next step asks for the buffer again), LBM_E_DEVICE. */
+lbm_status lbm_use_blocks(lbm_ctx *ctx, int32_t enable);
 
 void lbm_destroy(lbm_ctx *ctx);
 

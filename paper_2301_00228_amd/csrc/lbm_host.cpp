@@ -173,10 +173,11 @@ struct lbm_ctx {
 
   // Block passes (k_block): several steps of every plate per launch, in place
   // of the tile launches.  can_block: the plan was made (see plan_blocks);
-  // block: in use -- from the start, and under a tiling with steps = 2, which
-  // asks for several steps per pass; not under one with steps = 1.
+  // want_block: from the start, and under a tiling with steps = 2, which asks for
+  // several steps per pass; not under one with steps = 1; allow_block:
+  // lbm_use_blocks; block: all three (see pick_path).
   PatchPlan plan;
-  bool can_block = false;
+  bool can_block = false, want_block = true, allow_block = true;
   bool tiles_up = false;  // the device's tile lists are those of the tiling (see ready)
   bool tables = false;    // the tiles' prologue lists are in place (see ensure_tables)
   bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
@@ -1654,6 +1655,8 @@ lbm_status ensure_ahead(lbm_ctx *c) {
   return LBM_OK;
 }
 
+void pick_path(lbm_ctx *c) { c->block = c->can_block && c->want_block && c->allow_block; }
+
 // What the launches of the path in use read and write is in place (also after a
 // call that could not finish: for want of memory, say, it leaves the lists of
 // another tiling, or none): the tile lists, and for the tile launches their
@@ -2183,7 +2186,8 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
   c->rows = 8;
   c->edge_rows = 2;
   c->align = c->n_body < ((int64_t)4 << 20) ? 0 : 16;
-  c->block = c->can_block = plan_blocks(c);
+  c->can_block = plan_blocks(c);
+  pick_path(c);
   if (new_tiles(c) != LBM_OK) return bail(LBM_E_NOMEM, c->err);
   if (hipEventCreateWithFlags(&c->flag_ev, hipEventDisableTiming) != hipSuccess)
     return bail(LBM_E_DEVICE, "event creation failed");
@@ -2462,7 +2466,8 @@ lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
   c->nt = stream;
   c->two = steps == 2 ? 1 : 0;
   c->tiled = true;
-  c->block = c->can_block && c->two;
+  c->want_block = c->two != 0;
+  pick_path(c);
   if (c->two && !c->block) {
     lbm_status st3 = ensure_third(c);
     if (st3) {
@@ -2486,6 +2491,16 @@ lbm_status lbm_use_overlap(lbm_ctx *c, int32_t enable) {
   c->overlap = enable != 0;
   // (the frame tiles are cut shorter with overlapped pairs)
   return new_tiles(c);
+}
+
+lbm_status lbm_use_blocks(lbm_ctx *c, int32_t enable) {
+  if (!c) return LBM_E_INVAL;
+  if (c->allow_block == (enable != 0)) return LBM_OK;
+  HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");
+  drop_graph(c);
+  c->allow_block = enable != 0;
+  pick_path(c);
+  return ready(c);
 }
 
 lbm_status lbm_profile(lbm_ctx *c, int64_t n, double *ms, int64_t *launches) {
@@ -2913,7 +2928,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   // The block pass, timed as lbm_step runs it (from buffer cur to the other
   // one, which the steps below write anyway).
   bool use_block = false;
-  if (c->can_block) {
+  if (c->can_block && c->allow_block) {
     reps = std::max(steps, std::min(400, (int)std::ceil(5.0 / std::max(best, 1e-4) / c->plan.K)));
     const double per = time_body([&](hipStream_t st2, int k) {
       hipError_t e = hipSuccess;
@@ -2944,7 +2959,8 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   c->nt = bt.stream_stores;
   c->two = bt.steps == 2 ? 1 : 0;
   c->overlap = best_ov;
-  c->block = use_block;
+  if (c->allow_block) c->want_block = use_block;
+  pick_path(c);
   c->tiled = true;
   if ((!c->two || c->block) && !had_third) release_third(c);
   st = new_tiles(c);

@@ -26,6 +26,7 @@ READ_FLUX_STREAMED, READ_EQ_OLD = 1, 2
 # Every entry point declared in include/lbm.h.
 EXPORTS = ["lbm_create", "lbm_set_bc", "lbm_step", "lbm_fields", "lbm_fields_device", "lbm_info",
            "lbm_set_tiling", "lbm_autotune", "lbm_profile", "lbm_use_graphs", "lbm_use_overlap", "lbm_destroy",
+           "lbm_use_blocks",
            "lbm_last_error", "lbm_version", "lbm_exact_cells", "lbm_consistency_error",
            "lbm_fields_noalloc", "lbm_prepare_steps", "lbm_copy_rate",
            "lbm_layout_copy_rate"]
@@ -125,6 +126,8 @@ def library():
     L.lbm_use_graphs.argtypes = [vp, C.c_int32]
     L.lbm_use_overlap.restype = C.c_int
     L.lbm_use_overlap.argtypes = [vp, C.c_int32]
+    L.lbm_use_blocks.restype = C.c_int
+    L.lbm_use_blocks.argtypes = [vp, C.c_int32]
     L.lbm_destroy.restype = None
     L.lbm_destroy.argtypes = [vp]
     L.lbm_last_error.restype = C.c_char_p
@@ -398,6 +401,11 @@ class Context:
         """lbm_use_overlap: deep two-step tiles on a second stream beside the
         single-step launches (default on; bitwise the same results)."""
         self._check(library().lbm_use_overlap(self._h, int(bool(on))))
+
+    def use_blocks(self, on=True):
+        """lbm_use_blocks: several steps per launch where possible (default on),
+        or the tile launches of the tiling (bitwise the same results)."""
+        self._check(library().lbm_use_blocks(self._h, int(bool(on))))
 
 
 def plate_dict(case):
