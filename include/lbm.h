@@ -287,6 +287,24 @@ typedef struct {
 } lbm_info_t;
 lbm_status lbm_info(const lbm_ctx *ctx, lbm_info_t *info);
 
+/* The block passes of a context (see lbm_step), whose tile_* values in
+ * lbm_info are those of its tile launches.  Filled by lbm_block_info (errors:
+ * LBM_E_INVAL on NULL). */
+typedef struct {
+  int32_t in_use;        /* 1: lbm_step takes block passes (single steps of large plates
+                            excepted); 0: tile launches                                  */
+  int32_t steps;         /* steps per pass at most (0, as all that follows: no block passes
+                            for these bodies)                                            */
+  int32_t rows;          /* rows per wave of the first launch (patches at boundaries, and
+                            others that fill it up)                                      */
+  int32_t inner_rows;    /* rows of a patch of the second launch (no boundary nodes)     */
+  int32_t patches;       /* patches of the first launch (0: there is none)               */
+  int32_t inner_patches; /* patches of the second launch (0: there is none)              */
+  int32_t edge_patches;  /* those of `patches` that hold boundary nodes                  */
+  int32_t pad;
+} lbm_block_info_t;
+lbm_status lbm_block_info(const lbm_ctx *ctx, lbm_block_info_t *info);
+
 /* Interior-kernel tiling.  A tile is a strip of columns times a band of
  * rows; one workgroup marches up (or down) its rows.
  *  lanes      workgroup size, 64, 128 or 256; a tile owns at most lanes-2

@@ -2443,6 +2443,20 @@ lbm_status lbm_info(const lbm_ctx *c, lbm_info_t *info) {
   return LBM_OK;
 }
 
+lbm_status lbm_block_info(const lbm_ctx *c, lbm_block_info_t *info) {
+  if (!c || !info) return LBM_E_INVAL;
+  std::memset(info, 0, sizeof *info);
+  info->in_use = c->block ? 1 : 0;
+  if (!c->can_block) return LBM_OK;
+  info->steps = c->plan.K;
+  info->rows = c->plan.rows;
+  info->inner_rows = c->plan.inner_rows;
+  info->patches = (int32_t)c->plan.patches.size();
+  info->inner_patches = (int32_t)c->plan.inner.size();
+  for (const Patch &t : c->plan.patches) info->edge_patches += t.b1 > t.b0 ? 1 : 0;
+  return LBM_OK;
+}
+
 lbm_status lbm_set_tiling(lbm_ctx *c, const lbm_tiling *t) {
   if (!c || !t) return LBM_E_INVAL;
   const int32_t lanes = t->lanes, rows = t->rows, order = t->order, edge_rows = t->edge_rows,

@@ -26,7 +26,7 @@ READ_FLUX_STREAMED, READ_EQ_OLD = 1, 2
 # Every entry point declared in include/lbm.h.
 EXPORTS = ["lbm_create", "lbm_set_bc", "lbm_step", "lbm_fields", "lbm_fields_device", "lbm_info",
            "lbm_set_tiling", "lbm_autotune", "lbm_profile", "lbm_use_graphs", "lbm_use_overlap", "lbm_destroy",
-           "lbm_use_blocks",
+           "lbm_use_blocks", "lbm_block_info",
            "lbm_last_error", "lbm_version", "lbm_exact_cells", "lbm_consistency_error",
            "lbm_fields_noalloc", "lbm_prepare_steps", "lbm_copy_rate",
            "lbm_layout_copy_rate"]
@@ -69,6 +69,11 @@ class lbm_info_t(C.Structure):
                 ("tile_edge_cols", C.c_int32), ("nodes_deep", C.c_int64), ("overlap", C.c_int32),
                 ("graphs_cached", C.c_int32), ("steps_in_graphs", C.c_int64),
                 ("syncs_done", C.c_int64), ("tile_stream_stores", C.c_int32), ("pad", C.c_int32)]
+
+
+class lbm_block_info_t(C.Structure):
+    _fields_ = [(f, C.c_int32) for f in ("in_use", "steps", "rows", "inner_rows", "patches",
+                                         "inner_patches", "edge_patches", "pad")]
 
 
 class lbm_tiling(C.Structure):
@@ -116,6 +121,8 @@ def library():
     L.lbm_fields_device.argtypes = [vp, C.c_int32, vp, vp, vp, vp]
     L.lbm_info.restype = C.c_int
     L.lbm_info.argtypes = [vp, C.POINTER(lbm_info_t)]
+    L.lbm_block_info.restype = C.c_int
+    L.lbm_block_info.argtypes = [vp, C.POINTER(lbm_block_info_t)]
     L.lbm_set_tiling.restype = C.c_int
     L.lbm_set_tiling.argtypes = [vp, C.POINTER(lbm_tiling)]
     L.lbm_autotune.restype = C.c_int
@@ -371,6 +378,12 @@ class Context:
         i = lbm_info_t()
         self._check(library().lbm_info(self._h, C.byref(i)))
         return {f: getattr(i, f) for f, _ in lbm_info_t._fields_}
+
+    def block_info(self):
+        """lbm_block_info: the block passes in use and their patches."""
+        i = lbm_block_info_t()
+        self._check(library().lbm_block_info(self._h, C.byref(i)))
+        return {f: getattr(i, f) for f, _ in lbm_block_info_t._fields_ if f != "pad"}
 
     def set_tiling(self, lanes, rows, order=0, edge_rows=0, align=0, steps=1, edge_cols=0,
                    stream_stores=0):
