@@ -1712,14 +1712,47 @@ struct BlockShape {
   int K, rows, inner;
 };
 
+// Predicted us per step.
+//
+// Block passes: per pass about 12 + K m units with m rows per wave (a unit is 0.4
+// us in FP32, 0.5 in FP64 without boundary nodes, 0.6 and 0.85 with them: 256^2
+// clamped FP64, us per pass: m = 3, K = 3, 4, 5 16.9, 19.6, 21.9; m = 4, K = 4, 5, 6
+// 26.0, 28.9, 33.0), once per round of patches over the CUs; patches without
+// boundary nodes (k_inner) at 4 TB/s of their reads and writes.  Perforated bodies
+// of 600^2 and 1800^2 (holes of radius 2.5 to 30, 8 to 128 nodes apart) measure 0.8
+// to 1.3 of it; 1.3 times as long under readings other than R1 and M1.
+double block_unit(const lbm_ctx *c) {
+  return (c->storage == LBM_STORE_F64 ? 0.85 : 0.6) * (c->variant_readings ? 1.3 : 1);
+}
+double block_us(const lbm_ctx *c, const PatchPlan &q) {
+  const double per_node = 0.5 * bytes_per_update(c->storage);
+  double own = 0;
+  for (const Patch &t : q.inner) own += (double)(t.ox1 - t.ox0) * (t.oy1 - t.oy0);
+  const double bytes = per_node * (own + (double)q.inner.size() * kBlockCols * q.inner_rows);
+  const int64_t rounds = ((int64_t)q.patches.size() + kCus - 1) / kCus;
+  return ((double)rounds * (12 + q.K * q.rows) * block_unit(c) + bytes / 4e6) / q.K;
+}
+
+// Tile launches (one step each) of bodies dense in boundary nodes: a third to over
+// half of the nodes at a boundary, ns per node in FP64 0.26 to 0.35, FP32 0.16 to
+// 0.22, F32DEV 0.17 to 0.29, 16-bit 0.15 to 0.27; 14 us for the launch at least.
+// (Of bodies with fewer boundary nodes it is up to three times too long, but
+// there block passes take half of what they take or less.)  Under readings other than
+// R1 and M1, with a boundary launch besides, 1.1 times that in FP64 and FP32, 1.4 in
+// the others.
+double tile_us(const lbm_ctx *c) {
+  const double ns = c->storage == LBM_STORE_F64      ? 0.30
+                    : c->storage == LBM_STORE_F32    ? 0.19
+                    : c->storage == LBM_STORE_F32DEV ? 0.24
+                                                     : 0.21;
+  return std::max(14.0, 1e-3 * ns * (double)c->n_body) * (c->variant_readings ? 1.2 : 1);
+}
+
 // The plan of the block pass.
 //
-// Small plates are bound by a pass's latency, about 12 + K m units with m rows
-// per wave (a unit is 0.4 us in FP32, 0.5 in FP64 without boundary nodes, 0.6 and
-// 0.85 with them: 256^2 clamped FP64, us per pass: m = 3, K = 3, 4, 5 16.9, 19.6,
-// 21.9; m = 4, K = 4, 5, 6 26.0, 28.9, 33.0), once per round of patches over the
-// CUs: the shape with the least of that per step is taken, all patches in one
-// launch.  Past one round in FP64, two in the 4-byte storages, throughput counts
+// Small plates are bound by a pass's latency (block_us): the shape with the least
+// of that per step is taken, all patches in one launch.  Past one round in FP64,
+// two in the 4-byte storages, throughput counts
 // instead: patches without boundary nodes go to k_inner, two to a CU, and are as
 // large as that leaves registers for.  Us per step, one launch / two: within a
 // round 640^2 FP32 6.3 / 9.0; at two 1031 x 517 FP32 8.7 / 9.2, F16DEV 11.1 / 11.6,
@@ -1728,11 +1761,21 @@ struct BlockShape {
 // K is there where the halo's growth meets the passes saved: 4096^2 with
 // a hole, K = 4, 5, 6: FP64 258, 209, 217; FP32 141, 116, 107; F32DEV 170, 138,
 // 129; F16DEV 157, 132, 149.
+//
+// Where boundary nodes lie close together that K leaves a patch few nodes of its
+// own, or cannot be cut: fewer steps per pass are then tried, the least of block_us
+// taken, and tile launches if those are predicted to be faster (us per step, tile
+// launches / the large plates' K / the one taken: holes of radius 4 every 12 nodes,
+// 600^2 F32DEV 36 / 56 / 20 (K = 3), FP64 54 / 42 / 30 (2), FP32 31 / 43 / 26 (4); bars
+// three wide every 9, 1800^2 F32DEV 508 / 7107 / 348 (2); bars two wide every 8, 600^2
+// FP64 53 / 467 / tiles).  Not tried where the prediction is under half of the
+// tiles': radius 8 every 32, 1800^2 FP64 377 / 230 / 198 (3).
 bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &plan) {
   const bool f64 = c->storage == LBM_STORE_F64, bounded = !c->bnd.empty();
   const int R = block_inner_rows(c->storage);
+  const bool variant = c->variant_readings && bounded;
   std::vector<BlockShape> small;
-  if (c->variant_readings && bounded)
+  if (variant)
     small = {};
   else if (!bounded)
     small = {{6, 3, kInnerSmall}, {5, 3, kInnerSmall}, {4, 3, kInnerSmall}};
@@ -1752,38 +1795,46 @@ bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &
     const int64_t least = std::max<int64_t>((int64_t)v.size(), c->n_body / own);
     if (least > most || (best > 0 && cost(b, least) >= best)) continue;
     PatchPlan q;
-    if (!make_patch_plan(v, b.K, b.rows, b.inner, q)) continue;
+    if (!make_patch_plan(v, b.K, b.rows, b.inner, q, most)) continue;
     const int64_t n = (int64_t)(q.patches.size() + q.inner.size());
-    if (n > most || (best > 0 && cost(b, n) >= best)) continue;
+    if (best > 0 && cost(b, n) >= best) continue;
     best = cost(b, n);
     plan = std::move(q);
   }
   // patches without boundary nodes that k_block takes: all on small plates with
   // some, else as many as fill its last round of CUs
-  auto fill = [&](size_t n) {
-    n = std::min(n, plan.inner.size());
-    plan.patches.insert(plan.patches.end(), plan.inner.end() - (int64_t)n, plan.inner.end());
-    plan.inner.resize(plan.inner.size() - n);
+  auto fill = [&](PatchPlan &q, size_t n) {
+    n = std::min(n, q.inner.size());
+    q.patches.insert(q.patches.end(), q.inner.end() - (int64_t)n, q.inner.end());
+    q.inner.resize(q.inner.size() - n);
   };
   if (best > 0) {
-    if (bounded) fill(plan.inner.size());
+    if (bounded) fill(plan, plan.inner.size());
     return true;
   }
-  if (c->variant_readings && bounded) {
-    // (the flux and four populations pulled per boundary node leave LDS for three
-    // rows per wave in FP64)
-    if (!make_patch_plan(v, 5, 3, 24, plan) && !make_patch_plan(v, 4, 3, 24, plan)) return false;
-    fill(plan.inner.size());
-    return true;
-  }
-  const BlockShape large = f64 ? BlockShape{5, 4, R} : c->storage == LBM_STORE_F32 ? BlockShape{6, 6, R}
+  // (other readings: the flux and four populations pulled per boundary node leave
+  // LDS for three rows per wave in FP64, and one launch takes all patches)
+  const BlockShape large = variant ? BlockShape{5, 3, 24}
+                           : f64 ? BlockShape{5, 4, R} : c->storage == LBM_STORE_F32 ? BlockShape{6, 6, R}
                            : c->storage == LBM_STORE_F32DEV ? BlockShape{6, 5, R} : BlockShape{5, 5, R};
-  // (a plate too dense with boundary nodes for K steps may still do four)
-  if (!make_patch_plan(v, large.K, large.rows, large.inner, plan) &&
-      !make_patch_plan(v, 4, large.rows, large.inner, plan))
-    return false;
-  if (!plan.patches.empty()) fill((size_t)kCus - 1 - (plan.patches.size() + kCus - 1) % kCus);
-  return true;
+  const double tiles = tile_us(c);
+  for (int K = large.K; K >= 2; K--) {
+    // (a plan of more patches with boundary nodes than this is slower than the tiles;
+    // those without are few next to their nodes, and a plate takes one at least)
+    const int64_t limit = (int64_t)(tiles * K / ((12 + K * large.rows) * block_unit(c)) + 1) * kCus +
+                          (variant ? 0 : c->n_body / 64) + 2 * (int64_t)v.size();
+    PatchPlan q;
+    if (!make_patch_plan(v, K, large.rows, large.inner, q, limit)) continue;
+    if (variant) fill(q, q.inner.size());
+    const double us = block_us(c, q);
+    if (best > 0 && us >= best) continue;
+    // (tiny plates, each in one patch or two: no K cuts them into fewer)
+    best = q.patches.size() <= 2 * v.size() ? std::min(us, 0.4 * tiles) : us;
+    if (!variant && !q.patches.empty()) fill(q, (size_t)kCus - 1 - (q.patches.size() + kCus - 1) % kCus);
+    plan = std::move(q);
+    if (best < 0.5 * tiles) break;
+  }
+  return best > 0 && best < tiles;
 }
 
 // Cut the plates for the block pass and upload the plan (lbm_create).  False

@@ -36,9 +36,12 @@ struct PatchPlan {
 
 class PatchCutter {
  public:
-  PatchCutter(const PatchPlate &p, int K, int rows, int inner)
+  // made, most: patches made so far, of all plates; a cut that would make more
+  // than `most` fails
+  PatchCutter(const PatchPlate &p, int K, int rows, int inner, std::atomic<int64_t> *made = nullptr,
+              int64_t most = INT64_MAX)
       : p_(p), K_(K), hb_(rows * (kBlockThreads / 64 - 1)), hi_(inner),
-        ring_(3 * K + 4) {
+        ring_(3 * K + 4), made_(made), most_(most) {
     row0_.assign((size_t)p.ny + 1, 0);
     for (int64_t b = 0; b < p.nb; b++) row0_[(size_t)p.bnd[b].j + 1]++;
     for (int j = 0; j < p.ny; j++) row0_[(size_t)j + 1] += row0_[(size_t)j];
@@ -92,7 +95,8 @@ class PatchCutter {
     return v;
   }
 
-  // The patches of one band; false if some node's dependences do not fit.
+  // The patches of one band; false if some node's dependences do not fit, or past
+  // `most`.
   bool cut(const Band &b, PatchPlan &out) {
     bool ok = true;
     auto even = [&](int x0, int x1, int w) {
@@ -190,6 +194,8 @@ class PatchCutter {
   };
   PatchPlate p_;
   int K_, hb_, hi_, ring_;
+  std::atomic<int64_t> *made_;
+  int64_t most_;
   std::vector<int64_t> row0_;
   int lx_ = 0, ly_ = 0, gw_ = 0, gh_ = 0;
   std::vector<uint8_t> c_;
@@ -384,6 +390,7 @@ class PatchCutter {
       }
       return ok;
     }
+    if (made_ && ++*made_ > most_) return false;
     t.plate = p_.index;
     // (the rectangle's body nodes are all in the patch)
     t.ox0 = std::max(0, x0 - t.ex);
@@ -424,10 +431,13 @@ class PatchCutter {
 };
 
 // The plan for K steps with `rows` rows per wave (patches without boundary
-// nodes: `inner` rows at most) over all plates; false if some plate cannot be cut (a node's dependences exceed a patch).  Bands are
-// cut by several host threads; the result does not depend on their number.
+// nodes: `inner` rows at most) over all plates; false if some plate cannot be cut
+// (a node's dependences exceed a patch) or takes more than `most` patches, which
+// ends the cut there: a body too dense in boundary nodes for K steps would be cut
+// into tens of thousands (a second and more of host work).  Bands are cut by
+// several host threads; the result does not depend on their number.
 inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int rows, int inner,
-                            PatchPlan &plan) {
+                            PatchPlan &plan, int64_t most = INT64_MAX) {
   struct Job {
     int plate;
     PatchCutter::Band band;
@@ -444,6 +454,7 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
   }
   std::atomic<size_t> next{0};
   std::atomic<bool> failed{false};
+  std::atomic<int64_t> made{0};
   auto work = [&]() {
     try {
       int have = -1;
@@ -451,7 +462,7 @@ inline bool make_patch_plan(const std::vector<PatchPlate> &plates, int K, int ro
       for (size_t i = next++; i < jobs.size() && !failed; i = next++) {
         if (have != jobs[i].plate) {
           cutter.clear();
-          cutter.emplace_back(plates[(size_t)jobs[i].plate], K, rows, inner);
+          cutter.emplace_back(plates[(size_t)jobs[i].plate], K, rows, inner, &made, most);
           have = jobs[i].plate;
         }
         jobs[i].ok = cutter[0].cut(jobs[i].band, jobs[i].out);

@@ -71,8 +71,7 @@ def test_block_info_follows_the_settings():
 
 def perforated_everywhere(nx, ny, edge=3):
     """Single-node holes a knight's move apart: every node between them is a
-    boundary node, so four steps of one node depend on more of them than a
-    patch holds."""
+    boundary node, and a patch owns few of the nodes that two steps depend on."""
     y, x = np.mgrid[0:ny, 0:nx]
     m = ((x + 2 * y) % 5 != 0).astype(np.uint8)
     m[:edge], m[-edge:], m[:, :edge], m[:, -edge:] = 1, 1, 1, 1
@@ -81,8 +80,8 @@ def perforated_everywhere(nx, ny, edge=3):
 
 @pytest.mark.parametrize("storage", block.STORAGES)
 def test_a_body_without_a_plan_takes_the_tile_launches(storage):
-    case = block.clamped(70, 66)
-    case.mask = perforated_everywhere(70, 66)
+    case = block.clamped(400, 300)
+    case.mask = perforated_everywhere(400, 300)
     case.u0, case.bcs = case.u0 * case.mask, []
     with lbm.context_for(case, storage) as ctx:
         assert set(ctx.block_info().values()) == {0}
@@ -91,3 +90,24 @@ def test_a_body_without_a_plan_takes_the_tile_launches(storage):
     a, b = (block.run([case], storage, (5, 30), t) for t in (block.SINGLE, (64, 8, 0, 4, 0, 2, 4)))
     for k in block.FIELDS:
         assert np.array_equal(a[0][k], b[0][k]), k
+
+
+@pytest.mark.parametrize("readings", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("storage", block.STORAGES)
+def test_bodies_dense_in_boundary_nodes_bitwise(storage, readings):
+    # (fewer steps per pass than large plates take)
+    y, x = np.mgrid[0:500, 0:530]
+    steps = set()
+    for r, p in ((4.0, 12), (6.0, 16), (2.5, 8)):
+        case = block.clamped(530, 500, a0_phi=0.99)
+        cx, cy = (x + p / 2) % p - p / 2, (y + p / 2) % p - p / 2
+        m = (cx * cx + cy * cy >= r * r).astype(np.uint8)
+        m[:3], m[-3:], m[:, :3], m[:, -3:] = 1, 1, 1, 1
+        case.mask, case.u0, case.readings = m, case.u0 * m, readings
+        with lbm.context_for(case, storage) as ctx:
+            b = ctx.block_info()
+        assert b["in_use"], b
+        steps.add(b["steps"])
+        block.same([case], storage, (1, 6, 52))
+    print("steps per pass", steps)
+    assert min(steps) <= 3 and max(steps) <= 5
