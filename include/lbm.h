@@ -208,8 +208,8 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
  * synchronization after every l-th step).  Stream-ordered and asynchronous:
  * returns once the work is enqueued.  Several steps are taken per launch in
  * patches held in registers (block passes) unless a body is too dense in
- * boundary nodes to be cut into patches, the call is a single step of plates
- * too large for the Infinity Cache, lbm_set_tiling asked for one step per
+ * boundary nodes to be cut into patches, the call is a single step (or every step
+ * a synchronization) of plates too large for the Infinity Cache, lbm_set_tiling asked for one step per
  * launch, or lbm_use_blocks turned them off; the tile launches of a tiling (lbm_set_tiling) serve those cases,
  * with the same results bit for bit.  With two-step tile launches part of the work
  * runs on a second stream of the library's that forks from and joins back

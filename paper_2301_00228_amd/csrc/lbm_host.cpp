@@ -1682,17 +1682,20 @@ lbm_status before_steps(lbm_ctx *c) {
   return LBM_OK;
 }
 
-// A call of one step on plates whose state is past the Infinity Cache runs the
-// tile launches for its duration: there a block pass gains nothing but loads
-// and stores the patches' edges in a launch of its own (us, tiles / block: 2048^2
+// A call of one step, or of steps that each end in a synchronization, on plates
+// whose state is past the Infinity Cache runs the tile launches for its duration:
+// there a block pass gains nothing but loads and stores the patches' edges in a
+// launch of its own (us, tiles / block: 2048^2
 // FP64 242 / 266, 8192 x 1024 with holes 500 / 644, 4096^2 823 / 943; within it
-// 1024^2 73 / 66, 512^2 42 / 32).
+// 1024^2 73 / 66, 512^2 42 / 32; 20 steps with as many synchronizations, 4096^2 FP64
+// 28781 / 32256, FP32 16441 / 18977, 2048^2 F16DEV 4646 / 4799; within it 1024^2
+// 1830 / 1744; with a synchronization every second step 4096^2 FP64 22695 / 15960).
 struct TilesFor {
   lbm_ctx *c;
   bool block;
   int two;
   TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block), two(ctx->two) {
-    if (block && n == 1 && past_cache(c)) {
+    if (block && (n == 1 || c->sync_every == 1) && past_cache(c)) {
       c->block = false;
       c->two = 0;  // (no pairs)
     }
@@ -2581,6 +2584,7 @@ lbm_status lbm_profile(lbm_ctx *c, int64_t n, double *ms, int64_t *launches) {
     ~Restore() { c->block = block; }
   } restore{c, c->block};
   if (c->tiled) c->block = false;
+  const TilesFor tiles(c, n);
   st = before_steps(c);
   if (st) return st;
   // Launches on one stream go back to back; the time between the events

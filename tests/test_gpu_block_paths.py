@@ -111,3 +111,17 @@ def test_bodies_dense_in_boundary_nodes_bitwise(storage, readings):
         block.same([case], storage, (1, 6, 52))
     print("steps per pass", steps)
     assert min(steps) <= 3 and max(steps) <= 5
+
+
+def test_single_steps_and_synchronized_steps_of_large_plates_take_tiles():
+    # (a state past the 256 MB of the Infinity Cache, and one within it)
+    for n, large in ((1300, True), (700, False)):
+        for sync, calls, count, tiles in ((50, 1, 1, large), (1, 3, 3, large), (2, 4, 2, False)):
+            case = block.clamped(n, n - 7)
+            case.sync_every = sync
+            with lbm.context_for(case) as ctx:
+                kinds = ctx.profile(calls)
+            assert kinds["interior" if tiles else "two_step"][1] == count, (n, sync, kinds)
+            assert kinds["two_step" if tiles else "interior"][1] == 0, (n, sync, kinds)
+            assert kinds["sync"][1] == (calls // sync), (n, sync, kinds)
+            block.same([case], "f64", (4, 1, 7))
