@@ -1138,8 +1138,13 @@ bool past_cache(const lbm_ctx *c) {
 lbm_status ensure_tables(lbm_ctx *c) {
   if (c->tables) return LBM_OK;
   HIP_TRY(c, hipStreamSynchronize(c->stream), "synchronize");  // (launches that read the tiles)
-  build_tile_tables(c);
-  lbm_status st = upload_tiles(c);
+  lbm_status st = LBM_OK;
+  try {
+    build_tile_tables(c);
+    st = upload_tiles(c);
+  } catch (const std::bad_alloc &) {
+    return fail(c, LBM_E_NOMEM, "host memory for the prologue lists");
+  }
   if (st) return st;
   st = upload_tile_tables(c);
   if (st) return st;
@@ -1152,8 +1157,13 @@ lbm_status ensure_tables(lbm_ctx *c) {
 lbm_status new_tiles(lbm_ctx *c) {
   drop_graph(c);
   c->tables = c->tiles_up = false;
-  build_tiles(c);
-  return c->block && !past_cache(c) ? upload_tiles(c) : ensure_tables(c);
+  try {
+    build_tiles(c);
+    if (c->block && !past_cache(c)) return upload_tiles(c);
+  } catch (const std::bad_alloc &) {
+    return fail(c, LBM_E_NOMEM, "host memory for the tiles");
+  }
+  return ensure_tables(c);
 }
 
 lbm_status upload_boundary(lbm_ctx *c) {
@@ -1844,7 +1854,7 @@ bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &
 // if the tile launches have to do (the context stays usable): a plate whose
 // boundary nodes lie so densely that the nodes a small rectangle depends on do
 // not fit a patch, or no memory for the plan.
-bool plan_blocks(lbm_ctx *c) {
+bool plan_blocks(lbm_ctx *c) try {
   std::vector<PatchPlate> v(c->ph.size());
   for (size_t p = 0; p < v.size(); p++) {
     const PlateHost &h = c->ph[p];
@@ -1884,6 +1894,9 @@ bool plan_blocks(lbm_ctx *c) {
   c->d_ptasks = (PTask *)(d + t);
   c->d_pgrads = (PGrad *)(d + g);
   return true;
+} catch (const std::bad_alloc &) {
+  c->plan = PatchPlan();
+  return false;
 }
 
 // Rough magnitude of the initial fields for the 16-bit scale.
