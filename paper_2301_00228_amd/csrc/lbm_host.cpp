@@ -2185,11 +2185,18 @@ lbm_status lbm_create(const lbm_plate *plates, int32_t n_plates, lbm_storage sto
           hipMemset(c->ds.v[b][comp], 0, (size_t)N * uv_bytes(c->storage)) != hipSuccess)
         return bail(LBM_E_DEVICE, "memset");
     }
-  for (int p = 0; p < n_plates; p++) {
-    const PlateHost &h = c->ph[p];
-    if (hipMemcpy2D(c->d_cls + h.off, (size_t)h.pitch, h.cls.data(), (size_t)h.nx, (size_t)h.nx,
-                    (size_t)h.ny, hipMemcpyHostToDevice) != hipSuccess)
-      return bail(LBM_E_DEVICE, "class upload");
+  {
+    // (padded here and copied whole: a 2D copy takes 9 us per row, 9.6 ms of the
+    // 29 a 1024^2 context takes)
+    std::vector<uint8_t> rows;
+    for (int p = 0; p < n_plates; p++) {
+      const PlateHost &h = c->ph[p];
+      rows.assign((size_t)h.pitch * h.ny, 0);
+      for (int j = 0; j < h.ny; j++)
+        memcpy(rows.data() + (size_t)j * h.pitch, h.cls.data() + (size_t)j * h.nx, (size_t)h.nx);
+      if (hipMemcpy(c->d_cls + h.off, rows.data(), rows.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return bail(LBM_E_DEVICE, "class upload");
+    }
   }
   if (hipMemcpy(c->d_plates, c->pd.data(), c->pd.size() * sizeof(PlateDev),
                 hipMemcpyHostToDevice) != hipSuccess)
