@@ -95,3 +95,22 @@ def test_blocks_switched_mid_run():
     for a, b in zip(base, got):
         for k in FIELDS:
             assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f32dev", "f16dev", "bf16dev"])
+def test_long_runs_past_the_rim_and_the_outer_edges(storage):
+    """1500 steps of a pulse between a large hole and the outer edges, which it
+    reaches both: block passes, pairs and single steps, bit for bit (a
+    difference anywhere in the far field would have grown into all of it)."""
+    case = I.plate_with_hole(n=1200, radius=500, sigma=4.0, steps=0, a0_phi=0.99)
+    print("case", case.name, storage, flush=True)
+    calls = (700, 1, 799)
+    (base,) = _run([case], storage, calls)
+    rim = I.boundary_nodes(case.mask)
+    outer = (rim[:, 0] == 0) | (rim[:, 0] == 1199) | (rim[:, 1] == 0) | (rim[:, 1] == 1199)
+    for part in (rim[outer], rim[~outer]):  # (the pulse: u up to 1e-3 over 4 nodes)
+        assert np.abs(base["e"][part[:, 1], part[:, 0]]).max() > 1e-3 * (1e-3 / 4)
+    for tiling in ((128, 8, 0, 2, 0, 1), PAIRS):
+        (got,) = _run([case], storage, calls, tiling)
+        for k in FIELDS:
+            assert np.isfinite(base[k]).all() and np.array_equal(base[k], got[k]), (storage, tiling, k)
