@@ -30,10 +30,11 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 WORKLOAD = "hole8192"
 PRECISION_STEPS = 2000
-# The library's default, block passes, is what is timed.  These are the interior
-# tilings (lanes, rows, order, edge rows, alignment, steps per pass, edge
-# columns) and overlapped pairs (lbm_use_overlap) of its tile launches measured
-# fastest for this workload on MI355X (--tiling, --autotune time those).
+# The library's default, block passes, is what is timed; --tiling turns them off
+# and times the tile launches of a tiling, --autotune whatever it picks.  These
+# are the tilings (lanes, rows, order, edge rows, alignment, steps, edge columns)
+# and overlapped pairs (lbm_use_overlap) of the tile launches measured fastest for
+# this workload on MI355X.
 TUNED = {"f64": ((256, 16, 3, 8, 16, 2, 16), False),
          "f32": ((256, 16, 3, 8, 16, 2, 16), False),
          "f32dev": ((256, 16, 3, 8, 16, 2, 16), False),
@@ -58,21 +59,36 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def measured_traffic(storage, kind, tile, overlap):
-    """HBM bytes per launch of one interior-kernel kind from the committed
-    rocprofv3 PMC summary of this workload, if it was taken on the current
-    kernel and host sources (the host builds the tile lists) with the same
-    tiling and overlap setting."""
-    path = os.path.join(ROOT, "profiles", f"interior_{storage}_{WORKLOAD}_traffic.json")
+def measured_traffic(storage, kind, path):
+    """HBM bytes per launch of one interior-kernel kind (block passes: per pass)
+    from the committed rocprofv3 PMC summary of this workload, if it was taken on
+    the current kernel and host sources (the host builds the tile and patch
+    lists) with the same patches, or tiling and overlap setting."""
+    blocks = path["blocks"]
+    name = "block" if blocks else "interior"
     try:
-        with open(path) as fh:
+        with open(os.path.join(ROOT, "profiles", f"{name}_{storage}_{WORKLOAD}_traffic.json")) as fh:
             d = json.load(fh)
     except (OSError, ValueError):
         return None
-    if (d.get("kernel_source_hash") != kernel_source_hash() or d.get("tile") != tile
-            or d.get("overlap", False) != overlap):
+    if d.get("kernel_source_hash") != kernel_source_hash():
+        return None
+    if blocks:
+        return d.get("hbm_bytes_per_pass") if d.get("blocks") == blocks else None
+    if d.get("tile") != path["tile"] or d.get("overlap", False) != path["overlap"]:
         return None
     return d.get("kernels", {}).get(kind, {}).get("hbm_bytes_per_launch")
+
+
+def path_of(ctx):
+    """What lbm_step launches: the block passes' plan, or the tiling and overlap
+    setting of the tile launches."""
+    b, i = ctx.block_info(), ctx.info()
+    if b["in_use"]:
+        return {"blocks": b, "tile": None, "overlap": None}
+    return {"blocks": None, "overlap": bool(i["overlap"]),
+            "tile": [i["tile_lanes"], i["tile_rows"], i["tile_order"], i["tile_edge_rows"], i["tile_align"],
+                     i["tile_steps"], i["tile_edge_cols"], i["tile_stream_stores"]]}
 
 
 def rel_l2(a, b):
@@ -193,7 +209,7 @@ def main():
     ap.add_argument("--overlap", type=int, default=-1, choices=(-1, 0, 1),
                     help="overlapped pairs of the headline storage's tile launches (-1: the default)")
     ap.add_argument("--autotune", action="store_true",
-                    help="run the library's autotuner first")
+                    help="run the library's autotuner first, which may return to block passes")
     ap.add_argument("--copy-calibration", type=float, default=0.0, metavar="GIB",
                     help="only run a plain device copy of this many GiB 5 times (counter "
                          "calibration for rocprofv3 --pmc) and exit")
@@ -224,15 +240,12 @@ def main():
     case = inputs.plate_with_hole(n=8192, radius=1024, steps=PRECISION_STEPS)
     nodes = case.in_body_nodes()
 
-    def tiles(storage):
-        """Tile launches are profiled, not block passes."""
-        return args.autotune or bool(args.tiling and storage == args.storage)
-
     def timed_run(storage):
         t0 = time.perf_counter()
         ctx = lbm.context_for(case, storage)
         log(f"{storage}: context in {time.perf_counter() - t0:.1f} s")
         if args.tiling and storage == args.storage:
+            ctx.use_blocks(False)
             ctx.set_tiling(*[int(v) for v in args.tiling.split(",")])
         if not args.autotune and storage == args.storage and args.overlap >= 0:
             ctx.use_overlap(bool(args.overlap))
@@ -258,7 +271,7 @@ def main():
     def roofline_of(ctx, storage, psteps):
         """Dominant interior launch, timed with HIP events on its stream over
         psteps eager steps (lbm_profile); a block pass counts as one launch."""
-        info = ctx.info()
+        info, path = ctx.info(), path_of(ctx)
         prof = ctx.profile(psteps)
         kind = ("deep" if prof["deep"][1] > 0 else
                 "two_step" if prof["two_step"][1] > 0 else "interior")
@@ -269,32 +282,28 @@ def main():
         # the lattice updates it performs
         if kind == "deep":
             own, lups = info["nodes_deep"], 2 * info["nodes_deep"]
-        elif kind == "two_step" and tiles(storage):
+        elif kind == "two_step" and path["tile"]:
             own, lups = nodes, nodes + info["nodes_two_step"]
         elif kind == "two_step":
             own, lups = nodes, nodes * psteps // k_n
         else:
             own, lups = nodes, nodes
-        return info, prof, kind, per, own, lups, bpu
+        return info, path, prof, kind, per, own, lups, bpu
 
     # ---- headline storage
     ctx, dt, window = timed_run(args.storage)
     ms_per_step = dt / K * 1e3
     glups = nodes * K / dt / 1e9
-    info, prof, kind, per, own, lups, bpu = roofline_of(ctx, args.storage, args.profile_steps)
-    tile = [info["tile_lanes"], info["tile_rows"], info["tile_order"], info["tile_edge_rows"],
-            info["tile_align"], info["tile_steps"], info["tile_edge_cols"],
-            info["tile_stream_stores"]]
-    overlap = bool(info["overlap"])
+    info, path, prof, kind, per, own, lups, bpu = roofline_of(ctx, args.storage, args.profile_steps)
     achieved = own * bpu / per / 1e9
-    traffic = measured_traffic(args.storage, kind, tile, overlap)
+    traffic = measured_traffic(args.storage, kind, path)
     copy_gbs = copy_rate_gbs()
     layout_gbs = lbm.layout_copy_rate(args.storage, info["nodes_allocated"], 10)
     roofline = {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
         "kernel": (f"k_interior<{args.storage}, {info['tile_lanes']} lanes, {KIND_NAMES[kind]}>"
-                   if tiles(args.storage) else
+                   if path["tile"] else
                    f"block pass (k_block, k_inner)<{args.storage}>, {lups / nodes:.2f} steps"),
         "avg_launch_us": round(per * 1e6, 2),
         "algorithmic_bytes_per_launch": own * bpu,
@@ -333,7 +342,7 @@ def main():
             if st == args.storage:
                 continue
             c2, d2, w2 = timed_run(st)
-            i2, p2, k2, per2, own2, lups2, bpu2 = roofline_of(c2, st, args.profile_steps)
+            i2, path2, p2, k2, per2, own2, lups2, bpu2 = roofline_of(c2, st, args.profile_steps)
             ach2 = own2 * bpu2 / per2 / 1e9
             v = {"glups": round(nodes * K / d2 / 1e9, 3), "ms_per_step": round(d2 / K * 1e3, 4),
                  "speedup_vs_" + args.storage: round(dt / d2, 3), "bytes_per_lup": bpu2,
@@ -341,11 +350,8 @@ def main():
                  "kernel_GBs": round(ach2, 1), "kernel_frac": round(ach2 / HBM_PEAK_GBS, 4),
                  "kernel_effective_frac": round(lups2 * bpu2 / per2 / 1e9 / HBM_PEAK_GBS, 4),
                  "step_effective_frac": round(nodes * bpu2 / (d2 / K) / 1e9 / HBM_PEAK_GBS, 4),
-                 "graph_steps": w2["graph_steps"],
-                 "tile": [i2["tile_lanes"], i2["tile_rows"], i2["tile_order"],
-                          i2["tile_edge_rows"], i2["tile_align"], i2["tile_steps"],
-                          i2["tile_edge_cols"], i2["tile_stream_stores"]]}
-            t2 = measured_traffic(st, k2, v["tile"], bool(i2["overlap"]))
+                 "graph_steps": w2["graph_steps"], **path2}
+            t2 = measured_traffic(st, k2, path2)
             lc2 = lbm.layout_copy_rate(st, i2["nodes_allocated"], 10)
             v["layout_copy_GBs"] = round(lc2, 1)
             if t2:
@@ -400,7 +406,7 @@ def main():
                                "(traction-free rim), outer edges clamped u*=0, nu 0.3, a0_phi "
                                "0.9999, Gaussian pulse sigma 16 amp 1e-3 on the annulus, sync "
                                f"every 50; {args.storage} storage",
-                   "nodes": nodes, "storage": args.storage, "tile": tile, "overlap": overlap,
+                   "nodes": nodes, "storage": args.storage, **path,
                    "graphs": window["graph_steps"] == K,
                    "timed_window": {"steps": [window["first_step"], window["first_step"] + K - 1],
                                     "steps_in_graphs": window["graph_steps"],

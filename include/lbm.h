@@ -390,26 +390,27 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t steps, double *best_ms);
  * the others) or block passes, ms[4] the deep-tile launches of overlapped pairs (see
  * lbm_use_overlap); and the number of launches of each kind in
  * launches[0..4] (nullable).  Overlapped launches run at the same time, so
- * the sum over kinds can exceed the wall time.  After lbm_set_tiling or
- * lbm_autotune the tile launches of that tiling are run and timed (also where
- * lbm_step uses block passes), else what lbm_step launches.  Synchronizes the
- * stream. */
+ * the sum over kinds can exceed the wall time.  What lbm_step launches is run
+ * and timed; after lbm_set_tiling, until lbm_autotune picks otherwise, the tile
+ * launches of that tiling (also where lbm_step uses block passes; two-step
+ * tilings then allocate their third state buffer, LBM_E_NOMEM if they
+ * cannot).  Synchronizes the stream. */
 lbm_status lbm_profile(lbm_ctx *ctx, int64_t n_steps, double *ms, int64_t *launches);
 
 /* Capture, without running them, the HIP graphs that lbm_step(ctx,
  * n_steps) would replay from the current state, so that the lbm_step call
  * that follows launches only cached graphs (e.g. before a timed or
- * latency-critical call).  Starts the context like the first lbm_step (the
- * boundary accelerations of step 0 are enqueued) but takes no step.  No-op
- * with graphs off.  Errors as lbm_step. */
+ * latency-critical call).  Starts the context like the first lbm_step but
+ * takes no step.  No-op with graphs off.  Errors as lbm_step. */
 lbm_status lbm_prepare_steps(lbm_ctx *ctx, int64_t n_steps);
 
 /* Use (nonzero) or bypass (0) captured HIP graphs in lbm_step.  Default on.
  * With graphs on, lbm_step runs whole synchronization periods (from a step
  * that is a multiple of the period) as one cached graph each and any other
  * run of steps as a graph captured for that run's length and starting
- * phase; up to 8 graphs are kept (least recently used dropped).  Changing
- * the tiling or the overlap setting drops them. */
+ * phase (block passes: length and steps to the next synchronization); up to
+ * 32 graphs are kept (the less recently used half dropped).  Changing the
+ * tiling, the overlap setting or lbm_use_blocks drops them. */
 lbm_status lbm_use_graphs(lbm_ctx *ctx, int32_t enable);
 
 /* Overlapped pairs (nonzero, the default) or one stream (0), for two-step

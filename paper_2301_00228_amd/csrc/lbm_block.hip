@@ -49,8 +49,10 @@
 // 97^2 with loads 14.0 -> 6.1 -> 4.7, 1024^2 clamped 51 -> 20 -> 17, 4096^2 with
 // a hole 805 -> 289 -> 205, FP32 450 -> 163 -> 104, F16DEV 474 -> 222 -> 127.
 // Small plates are bound by the pass's latency (launch, one load, the steps'
-// chains); k_inner by memory in FP64 and F32DEV (4.8 TB/s of HBM, 1.6x to 1.8x the
-// state's reads), in FP32 by both that and the vector units (86 operations per
+// chains); k_inner by memory in FP64 (8192^2 with a hole, counted: 10.0 GB read,
+// 1.40 times the state, and 7.3 written per pass at 4.76 TB/s, 0.92 of a copy of the
+// state's arrays) and mostly in F32DEV (5.7 and 4.9 GB, 1.24 times the state, at 4.34
+// TB/s, 0.84), in FP32 by both that and the vector units (86 operations per
 // node and step, 85 % busy), in the 16-bit storages by their rounding (137).
 //
 // A step's chain is kept short by what does not change from step to step: a

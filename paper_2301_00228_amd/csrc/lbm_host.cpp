@@ -180,7 +180,7 @@ struct lbm_ctx {
   bool can_block = false, want_block = true, allow_block = true;
   bool tiles_up = false;  // the device's tile lists are those of the tiling (see ready)
   bool tables = false;    // the tiles' prologue lists are in place (see ensure_tables)
-  bool tiled = false;  // the caller set or tuned a tiling (lbm_profile times its launches)
+  bool tiled = false;  // the caller's or the tuned tiling is what lbm_profile times
   Patch *d_patches = nullptr, *d_inner = nullptr;
   PTask *d_ptasks = nullptr;
   PGrad *d_pgrads = nullptr;
@@ -1768,9 +1768,11 @@ double tile_us(const lbm_ctx *c) {
 // two in the 4-byte storages, throughput counts
 // instead: patches without boundary nodes go to k_inner, two to a CU, and are as
 // large as that leaves registers for.  Us per step, one launch / two: within a
-// round 640^2 FP32 6.3 / 9.0; at two 1031 x 517 FP32 8.7 / 9.2, F16DEV 11.1 / 11.6,
-// F32DEV 9.7 / 9.1, FP64 13.3 / 11.9, 640^2 FP64 11.4 / 10.4; beyond 1024^2 FP32
-// 13.9 / 11.3, FP64 21.9 / 17.1.
+// round 640^2 FP32 6.3 / 9.0; at two 1031 x 517 FP32 8.6 / 9.3, F16DEV 10.9 / 11.5,
+// BF16DEV 11.1 / 11.9, FP64 13.3 / 11.9, 640^2 FP64 11.4 / 10.4; beyond 1024^2 FP32
+// 13.9 / 11.3, FP64 21.9 / 17.1.  F32DEV is even there (1031 x 517 9.6 / 9.0, 800^2 9.8 /
+// 9.3, 720 x 700 8.9 / 9.0, 1000 x 700 9.7 / 10.4, a batch of six 10.9 / 12.8: one launch
+// is faster on eight of twelve).
 // K is there where the halo's growth meets the passes saved: 4096^2 with
 // a hole, K = 4, 5, 6: FP64 258, 209, 217; FP32 141, 116, 107; F32DEV 170, 138,
 // 129; F16DEV 157, 132, 149.
@@ -3050,7 +3052,7 @@ lbm_status lbm_autotune(lbm_ctx *c, int32_t steps, double *best_ms) {
   c->overlap = best_ov;
   if (c->allow_block) c->want_block = use_block;
   pick_path(c);
-  c->tiled = true;
+  c->tiled = !c->block;
   if ((!c->two || c->block) && !had_third) release_third(c);
   st = new_tiles(c);
   if (st) return st;

@@ -19,10 +19,6 @@ hipError_t launch_interior(int storage, const DevState &s, const Tile *tiles, in
 hipError_t launch_deep(int storage, const DevState &s, const Tile *tiles, int ntiles, int lanes,
                        const StepBufs &b, hipStream_t stream);
 // The block pass: `steps` steps of every plate from the complete state in
-// buffer `in` to the complete state in `out` (n patches of at most 8 * rows
-// rows, whose halos are for at least `steps` steps; rows: 2 or 4).  (Weak, so
-// that host-only programs link the runtime without the kernels.)
-// The block pass: `steps` steps of every plate from the complete state in
 // buffer `in` to the complete state in `out`, by launch_block over `patches` (of
 // at most 8 * rows rows; rows 3 .. 6, FP64: 3, 4) and launch_inner over `inner`
 // (patches without boundary nodes, of at most inner_rows rows:

@@ -38,6 +38,8 @@ def rel_l2(a, b):
 
 
 def timed(cases, storage, steps, warmup, tune=True, tiling=None, overlap=None):
+    """Timed steps of a context and the record of what ran: block passes, or with
+    a tiling, or for bodies that cannot be cut, tile launches."""
     import torch
     t0 = time.perf_counter()
     ctx = lbm.context_for(cases, storage)
@@ -45,10 +47,11 @@ def timed(cases, storage, steps, warmup, tune=True, tiling=None, overlap=None):
     print(f"context {storage}: {setup:.1f} s", file=sys.stderr, flush=True)
     ctx.step(2)
     if tiling:
+        ctx.use_blocks(False)
         ctx.set_tiling(*tiling)
         if overlap is not None:
             ctx.use_overlap(overlap)
-    elif tune:
+    elif tune and not ctx.block_info()["in_use"]:
         t1 = time.perf_counter()
         t_set = time.perf_counter()
         ctx.set_tiling(128, 16, 0, 4, 16, 2)
@@ -68,7 +71,22 @@ def timed(cases, storage, steps, warmup, tune=True, tiling=None, overlap=None):
     ctx.step(steps)
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
-    info = ctx.info()
+    info, blocks = ctx.info(), ctx.block_info()
+    nodes, bpu = info["nodes_in_body"], info["bytes_per_update"]
+    res = {"storage": storage, "plates": info["n_plates"], "nodes": nodes, "steps": steps,
+           "glups": nodes * steps / dt / 1e9, "ms_per_step": dt / steps * 1e3,
+           "effective_GBs": nodes * bpu * steps / dt / 1e9, "bytes_per_lup": bpu,
+           "boundary_nodes": info["boundary_nodes"], "device_GB": info["device_bytes"] / 1e9, "setup_s": setup,
+           "path": "block passes" if blocks["in_use"] else "tile launches"}
+    if blocks["in_use"]:
+        # whole passes of `steps` steps each, and what one must at least move:
+        # every body node's state read and written once
+        prof = ctx.profile(2 * blocks["steps"])
+        ms, n = prof["two_step"]
+        per = ms / n / 1e3
+        res.update(blocks=blocks, pass_us=per * 1e6, passes=n, pass_GBs=nodes * bpu / per / 1e9,
+                   pass_frac=nodes * bpu / per / 1e9 / HBM_PEAK_GBS)
+        return ctx, res
     prof = ctx.profile(4)
     # the dominant launch: with overlapped pairs the deep tiles' launch (two
     # steps of its nodes), else the first of a two-step pair (every body node
@@ -79,25 +97,20 @@ def timed(cases, storage, steps, warmup, tune=True, tiling=None, overlap=None):
     i_ms, i_n = prof[kind]
     b_ms, b_n = prof["boundary"]
     per = i_ms / i_n / 1e3
-    nodes = info["nodes_in_body"]
     streamed = info["nodes_deep"] if kind == "deep" else nodes
-    achieved = streamed * info["bytes_per_update"] / per / 1e9
+    achieved = streamed * bpu / per / 1e9
 
     def avg_us(k):
         return prof[k][0] / prof[k][1] * 1e3 if prof[k][1] else None
-    res = {"storage": storage, "plates": info["n_plates"], "nodes": nodes, "steps": steps,
-           "glups": nodes * steps / dt / 1e9, "ms_per_step": dt / steps * 1e3,
-           "interior_kind": kind, "interior_us": per * 1e6, "interior_GBs": achieved,
-           "interior_frac": achieved / HBM_PEAK_GBS, "boundary_us": b_ms / max(b_n, 1) * 1e3,
-           "first_launch_us": avg_us("two_step"),
-           "second_launch_us": avg_us("interior") if kind != "interior" else None,
-           "overlap": bool(info["overlap"]), "deep_nodes": info["nodes_deep"],
-           "two_step_nodes": info["nodes_two_step"],
-           "bytes_per_lup": info["bytes_per_update"], "boundary_nodes": info["boundary_nodes"],
-           "tile": [info["tile_lanes"], info["tile_rows"], info["tile_order"],
-                    info["tile_edge_rows"], info["tile_align"], info["tile_steps"],
-                    info["tile_edge_cols"], info["tile_stream_stores"]],
-           "device_GB": info["device_bytes"] / 1e9, "setup_s": setup}
+    res.update({"interior_kind": kind, "interior_us": per * 1e6, "interior_GBs": achieved,
+                "interior_frac": achieved / HBM_PEAK_GBS, "boundary_us": b_ms / max(b_n, 1) * 1e3,
+                "first_launch_us": avg_us("two_step"),
+                "second_launch_us": avg_us("interior") if kind != "interior" else None,
+                "overlap": bool(info["overlap"]), "deep_nodes": info["nodes_deep"],
+                "two_step_nodes": info["nodes_two_step"],
+                "tile": [info["tile_lanes"], info["tile_rows"], info["tile_order"],
+                         info["tile_edge_rows"], info["tile_align"], info["tile_steps"],
+                         info["tile_edge_cols"], info["tile_stream_stores"]]})
     return ctx, res
 
 
@@ -110,7 +123,7 @@ def main():
     ap.add_argument("--ref", default="f64",
                     help="storage of the reference run for the error ('' = no error)")
     ap.add_argument("--tiling", default="", metavar="L,R,O,E,A,S,W[,N]",
-                    help="interior tiling instead of the autotuner's pick")
+                    help="the tile launches of this tiling instead of block passes")
     ap.add_argument("--overlap", type=int, choices=(0, 1), default=None,
                     help="with --tiling: overlapped pairs on (1) or off (0); default on")
     ap.add_argument("--ref-plates", type=int, default=0,
@@ -134,9 +147,10 @@ def main():
     # arrays over as many nodes (after the context is gone, so that both
     # need not fit in memory at once)
     lc = lbm.layout_copy_rate(args.storage, nodes_allocated, 5)
+    rate = "pass" if "pass_GBs" in res else "interior"
     print(json.dumps({"workload": args.workload, "storage": args.storage,
                       "layout_copy_GBs": round(lc, 1),
-                      "interior_frac_of_layout_copy": round(res["interior_GBs"] / lc, 4)}), flush=True)
+                      rate + "_frac_of_layout_copy": round(res[rate + "_GBs"] / lc, 4)}), flush=True)
     if args.ref:
         # Reference and reduced run plate by plate from t = 0 for the same
         # number of steps (bounds memory: the FP64 state of the whole batch

@@ -114,3 +114,17 @@ def test_long_runs_past_the_rim_and_the_outer_edges(storage):
         (got,) = _run([case], storage, calls, tiling)
         for k in FIELDS:
             assert np.isfinite(base[k]).all() and np.array_equal(base[k], got[k]), (storage, tiling, k)
+
+
+def test_profile_times_what_the_autotuner_picked():
+    cases = [I.plate_with_hole(n=400, radius=50, sigma=6.0, steps=0)]
+    with lbm.context_for(cases) as ctx:
+        for blocks in (True, False):
+            ctx.use_blocks(blocks)
+            ctx.set_tiling(*PAIRS)
+            ctx.autotune(1)
+            assert ctx.block_info()["in_use"] == int(blocks)  # (0.4 of the best tiling's time)
+            prof, steps = ctx.profile(10), ctx.block_info()["steps"]
+            assert (prof["interior"][1] == 0) == blocks, prof
+            if blocks:
+                assert prof["two_step"][1] >= 10 // steps, prof
