@@ -216,7 +216,11 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
  * into the context's stream with events within the call (see
  * lbm_use_overlap), so to the caller the work is ordered on the context's
  * stream.  A blow-up detected by earlier work is reported as
- * LBM_E_NONFINITE by this or the next synchronizing call. */
+ * LBM_E_NONFINITE by this or the next synchronizing call.
+ * With graphs off (lbm_use_graphs) the launches may be captured into a graph of
+ * the caller's, once a step was taken before: of an even number of steps it ends
+ * in the state buffer it began in, so that every replay takes the next steps
+ * (with the synchronizations where the captured call had them). */
 lbm_status lbm_step(lbm_ctx *ctx, int64_t n_steps);
 
 /* Copy one plate's state to host buffers (any may be NULL): e = sum of the

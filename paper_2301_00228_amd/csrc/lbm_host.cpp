@@ -190,6 +190,7 @@ struct lbm_ctx {
   bool ahead = false;
 
   bool use_graphs = true;
+  bool captured = false;  // the call's launches go into a graph of the caller's
   // Captured step graphs, keyed by what the launch sequence of k steps from
   // step s depends on: k, s modulo lcm(l, 2) (synchronization points, step
   // parity), s == 0 (the first step of a run differs) and the buffers (cur,
@@ -1327,12 +1328,16 @@ hipError_t enqueue_segment(lbm_ctx *c, int64_t s, int64_t k, int &cur, int &prev
   const int T = 2;  // intermediate buffer of a two-step pair
   hipError_t e = hipSuccess;
   if (c->block) {
-    for (int64_t n = s; n < s + k && e == hipSuccess;) {
-      const int q = (int)std::min<int64_t>(c->plan.K, s + k - n), in = cur;
+    int64_t passes = (k + c->plan.K - 1) / c->plan.K, left = k;
+    // (a caller's graph of an even number of steps ends in the buffer it began in,
+    // as launches of one step each do, so that a replay goes on where the last ended)
+    if (c->captured && ((passes ^ k) & 1)) passes++;
+    for (; passes > 0 && e == hipSuccess; passes--) {
+      const int q = (int)std::min<int64_t>(c->plan.K, left - (passes - 1)), in = cur;
       e = timed(3, st, [&] { return enqueue_block(c, in, q, st); });
       prev = cur;
       cur ^= 1;
-      n += q;
+      left -= q;
     }
     if (e == hipSuccess && c->sync_every > 0 && (s + k) % c->sync_every == 0) {
       const int b = cur;
@@ -1682,6 +1687,13 @@ lbm_status ready(lbm_ctx *c) {
   return st || !c->two ? st : ensure_third(c);
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 // What has to be in place before steps are enqueued from the current state;
 // a block pass leaves no boundary accelerations for the next step.
 lbm_status before_steps(lbm_ctx *c) {
@@ -1781,10 +1793,10 @@ double tile_us(const lbm_ctx *c) {
 // own, or cannot be cut: fewer steps per pass are then tried, the least of block_us
 // taken, and tile launches if those are predicted to be faster (us per step, tile
 // launches / the large plates' K / the one taken: holes of radius 4 every 12 nodes,
-// 600^2 F32DEV 36 / 56 / 20 (K = 3), FP64 54 / 42 / 30 (2), FP32 31 / 43 / 26 (4); bars
-// three wide every 9, 1800^2 F32DEV 508 / 7107 / 348 (2); bars two wide every 8, 600^2
-// FP64 53 / 467 / tiles).  Not tried where the prediction is under half of the
-// tiles': radius 8 every 32, 1800^2 FP64 377 / 230 / 198 (3).
+// 600^2 F32DEV 36 / 56 / 22 (K = 4), FP64 53 / 42 / 35 (4), FP32 31 / 43 / 26 (4); bars
+// three wide every 9, 1800^2 F32DEV 508 / 7107 / 349 (2); bars two wide every 8, 600^2
+// FP64 52 / 467 / 52 (tiles)).  Not tried where the prediction is under half of the
+// tiles': radius 8 every 32, 1800^2 FP64 377 / 230 / 230 (198 with K = 3).
 bool choose_plan(const lbm_ctx *c, const std::vector<PatchPlate> &v, PatchPlan &plan) {
   const bool f64 = c->storage == LBM_STORE_F64, bounded = !c->bnd.empty();
   const int R = block_inner_rows(c->storage);
@@ -2344,6 +2356,11 @@ lbm_status lbm_step(lbm_ctx *c, int64_t n) {
     st = before_steps(c);
     if (st) return st;
   }
+  struct Captured {  // (for this call)
+    lbm_ctx *c;
+    ~Captured() { c->captured = false; }
+  } captured{c};
+  c->captured = !c->use_graphs && capturing(c->stream);
   while (n > 0) {
     if (c->use_graphs) {
       const int64_t k = graph_chunk(c, c->step, n);
