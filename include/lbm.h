@@ -208,8 +208,9 @@ lbm_status lbm_exact_cells(int32_t nx, int32_t ny, uint8_t periodic_x, uint8_t p
  * synchronization after every l-th step).  Stream-ordered and asynchronous:
  * returns once the work is enqueued.  Several steps are taken per launch in
  * patches held in registers (block passes) unless a body is too dense in
- * boundary nodes to be cut into patches, the call is a single step (or every step
- * a synchronization) of plates too large for the Infinity Cache, lbm_set_tiling asked for one step per
+ * boundary nodes to be cut into patches, the call (or the run between two
+ * synchronizations) is a single step of plates too large for the Infinity Cache,
+ * or one or a few of thin plates and batches of small ones, lbm_set_tiling asked for one step per
  * launch, or lbm_use_blocks turned them off; the tile launches of a tiling (lbm_set_tiling) serve those cases,
  * with the same results bit for bit.  With two-step tile launches part of the work
  * runs on a second stream of the library's that forks from and joins back
@@ -295,8 +296,8 @@ lbm_status lbm_info(const lbm_ctx *ctx, lbm_info_t *info);
  * lbm_info are those of its tile launches.  Filled by lbm_block_info (errors:
  * LBM_E_INVAL on NULL). */
 typedef struct {
-  int32_t in_use;        /* 1: lbm_step takes block passes (single steps of large plates
-                            excepted); 0: tile launches                                  */
+  int32_t in_use;        /* 1: lbm_step takes block passes (calls of a step or a few may
+                            not, see lbm_step); 0: tile launches                         */
   int32_t steps;         /* steps per pass at most (0, as all that follows: no block passes
                             for these bodies)                                            */
   int32_t rows;          /* rows per wave of the first launch (patches at boundaries, and

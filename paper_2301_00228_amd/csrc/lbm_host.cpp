@@ -185,6 +185,7 @@ struct lbm_ctx {
   PTask *d_ptasks = nullptr;
   PGrad *d_pgrads = nullptr;
   bool block = false;
+  int tile_calls = 0;  // calls of as many steps take the tile launches (see tile_calls)
   // the boundary nodes' u(t_{step+1}) is in the buffers the next step writes
   // (the tile launches expect it there; the block pass computes it itself)
   bool ahead = false;
@@ -1133,6 +1134,53 @@ bool past_cache(const lbm_ctx *c) {
   return (double)c->n_body * bytes_per_update(c->storage) > kInfinityCacheBytes;
 }
 
+// CUs of the GPU: workgroups of k_block that run at once.
+constexpr int kCus = 256;
+
+// us of a unit of a block pass (see block_us).
+double block_unit(const lbm_ctx *c) {
+  return (c->storage == LBM_STORE_F64 ? 0.85 : 0.6) * (c->variant_readings ? 1.3 : 1);
+}
+
+// The longest call (steps) that takes the tile launches although block passes are
+// in use; 0: none does.
+//
+// One step of plates past the Infinity Cache: a block pass gains nothing there but
+// loads and stores the patches' edges in a launch of its own (us, tiles / block: 2048^2
+// FP64 242 / 266, 8192 x 1024 with holes 500 / 644, 4096^2 823 / 943; within it
+// 1024^2 73 / 66, 512^2 42 / 32; 20 steps with as many synchronizations, 4096^2 FP64
+// 28781 / 32256, FP32 16441 / 18977, 2048^2 F16DEV 4646 / 4799; within it 1024^2
+// 1830 / 1744; with a synchronization every second step 4096^2 FP64 22695 / 15960).
+//
+// Else by prediction where patches take several rounds of the CUs, which thin
+// plates and batches of small ones do: a pass of n steps takes 11 us and n m + 12
+// units per round and moves the other patches at 7 TB/s (5 past the cache), n tile
+// launches 8 us each and 8 at the end, 5.5 ns per tile and the state at that rate.
+// (One step, tiles / block: 100 plates of sides 60 to 100 FP64 63 / 102, FP32 47 / 67;
+// 20000 x 4 FP64 26 / 41; 100000 x 12 FP32 57 / 165, two steps 134 / 196; but 4 x 20000
+// 72 / 42.  Tiles from 0.8 of the prediction down, for more steps 0.6: of 138 plates
+// and calls within the cache none then loses more than a seventh.)
+int tile_calls(const lbm_ctx *c) {
+  if (!c->can_block) return 0;
+  const double bytes = (double)c->n_body * bytes_per_update(c->storage);
+  const double rate = past_cache(c) ? 5e6 : 7e6;
+  const PatchPlan &p = c->plan;
+  double own = 0;
+  for (const Patch &t : p.inner) own += (double)(t.ox1 - t.ox0) * (t.oy1 - t.oy0);
+  const double inner =
+      0.5 * bytes_per_update(c->storage) * (own + (double)p.inner.size() * kBlockCols * p.inner_rows);
+  const int64_t rounds = ((int64_t)p.patches.size() + kCus - 1) / kCus;
+  const double launch = std::max(8.0, 5.5e-3 * (double)c->tiles.size() + bytes / rate);
+  int n = past_cache(c) ? 1 : 0;
+  for (; rounds > 1 && n < p.K; n++) {
+    const int k = n + 1;
+    const double block = 11 + (double)rounds * (12 + k * p.rows) * block_unit(c) + inner / rate;
+    const double tiles = (8 + k * (8 + launch)) * (c->variant_readings ? 1.2 : 1);
+    if (tiles >= (k == 1 ? 0.8 : 0.6) * block) break;
+  }
+  return n;
+}
+
 // The tiles' prologue lists, which only the tile launches read: built when they
 // first run (c->tables), since a context that takes block passes may never need
 // them (1.9 ms of host work at 1024^2); at once where calls of one step do.
@@ -1160,7 +1208,8 @@ lbm_status new_tiles(lbm_ctx *c) {
   c->tables = c->tiles_up = false;
   try {
     build_tiles(c);
-    if (c->block && !past_cache(c)) return upload_tiles(c);
+    c->tile_calls = tile_calls(c);
+    if (c->block && c->tile_calls == 0) return upload_tiles(c);
   } catch (const std::bad_alloc &) {
     return fail(c, LBM_E_NOMEM, "host memory for the tiles");
   }
@@ -1704,20 +1753,15 @@ lbm_status before_steps(lbm_ctx *c) {
   return LBM_OK;
 }
 
-// A call of one step, or of steps that each end in a synchronization, on plates
-// whose state is past the Infinity Cache runs the tile launches for its duration:
-// there a block pass gains nothing but loads and stores the patches' edges in a
-// launch of its own (us, tiles / block: 2048^2
-// FP64 242 / 266, 8192 x 1024 with holes 500 / 644, 4096^2 823 / 943; within it
-// 1024^2 73 / 66, 512^2 42 / 32; 20 steps with as many synchronizations, 4096^2 FP64
-// 28781 / 32256, FP32 16441 / 18977, 2048^2 F16DEV 4646 / 4799; within it 1024^2
-// 1830 / 1744; with a synchronization every second step 4096^2 FP64 22695 / 15960).
+// Runs the tile launches for the duration of a call of few steps, or of few from
+// one synchronization to the next, that they are faster for (see tile_calls).
 struct TilesFor {
   lbm_ctx *c;
   bool block;
   int two;
   TilesFor(lbm_ctx *ctx, int64_t n) : c(ctx), block(ctx->block), two(ctx->two) {
-    if (block && (n == 1 || c->sync_every == 1) && past_cache(c)) {
+    const int64_t run = c->sync_every > 0 ? std::min<int64_t>(n, c->sync_every) : n;
+    if (block && run > 0 && run <= c->tile_calls) {
       c->block = false;
       c->two = 0;  // (no pairs)
     }
@@ -1727,9 +1771,6 @@ struct TilesFor {
     c->two = two;
   }
 };
-
-// CUs of the GPU: workgroups of k_block that run at once.
-constexpr int kCus = 256;
 
 // Steps per pass, rows per wave of patches with boundary nodes, rows of those
 // without.
@@ -1746,9 +1787,6 @@ struct BlockShape {
 // boundary nodes (k_inner) at 4 TB/s of their reads and writes.  Perforated bodies
 // of 600^2 and 1800^2 (holes of radius 2.5 to 30, 8 to 128 nodes apart) measure 0.8
 // to 1.3 of it; 1.3 times as long under readings other than R1 and M1.
-double block_unit(const lbm_ctx *c) {
-  return (c->storage == LBM_STORE_F64 ? 0.85 : 0.6) * (c->variant_readings ? 1.3 : 1);
-}
 double block_us(const lbm_ctx *c, const PatchPlan &q) {
   const double per_node = 0.5 * bytes_per_update(c->storage);
   double own = 0;

@@ -125,3 +125,18 @@ def test_single_steps_and_synchronized_steps_of_large_plates_take_tiles():
             assert kinds["two_step" if tiles else "interior"][1] == 0, (n, sync, kinds)
             assert kinds["sync"][1] == (calls // sync), (n, sync, kinds)
             block.same([case], "f64", (4, 1, 7))
+
+
+@pytest.mark.parametrize("storage", block.STORAGES)
+def test_few_steps_of_thin_and_small_plates_take_tiles(storage):
+    small = [block.clamped(60 + 3 * k % 41, 60 + 7 * k % 41) for k in range(100)]
+    for cases, tiles in (([block.clamped(20000, 4)], 1), (small, 1 if storage == "f64" else None),
+                         ([block.clamped(4, 20000)], 0), ([block.clamped(300, 280)], 0)):
+        for n in (1, 7):
+            with lbm.context_for(cases, storage) as ctx:
+                assert ctx.block_info()["in_use"]
+                kinds = ctx.profile(n)
+            # (near the line in the 4-byte storages)
+            assert tiles is None or (kinds["interior"][1] > 0) == (n <= tiles), (cases[0].name, n, kinds)
+        print(cases[0].name, len(cases), flush=True)
+        block.same(cases, storage, (3, 1, 1, 2, 9, 1))
